@@ -57,7 +57,20 @@ void drop_graph(hipGraphExec_t *g) {
 constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
+// Prefill encodes the histories in chunks of positions: at least
+// PREFILL_CHUNK per sequence, and as many as make PREFILL_ROWS rows over the
+// batch where the workspace has the activation scratch for them. A chunk of
+// 16 positions is a pass of a few hundred rows, all launch and memory latency
+// (32 sequences x 512 events, d = 512, 8 layers: 32 chunks, 9.7 ms); 16384
+// rows give the products 128 x 128 tiles on every CU (one chunk, 2.4 ms with
+// the verify pass after it).
 constexpr int PREFILL_CHUNK = 16;
+constexpr int PREFILL_ROWS = 16384;
+// rows of the activation scratch that prefill uses for B sequences of up to cap events
+size_t prefill_rows(int B, int cap) {
+  const size_t want = std::max<size_t>(PREFILL_ROWS / B / PREFILL_CHUNK * PREFILL_CHUNK, PREFILL_CHUNK);
+  return (size_t)B * std::min<size_t>(want, std::max(cap, PREFILL_CHUNK));
+}
 
 // ---- packed weight layout -------------------------------------------------
 struct Entry {
@@ -187,7 +200,8 @@ struct ModelCache {
 
 struct tppsd_state {
   const tppsd_model *T = nullptr, *D = nullptr;
-  int B = 0, cap = 0, max_gamma = 0, Pmax = 0;
+  int B = 0, cap = 0, max_gamma = 0;
+  int chunk = 0;    // positions per sequence that a prefill pass encodes
   int kv_cap = 0;   // KV cache positions per (sequence, head): cap rounded up to 8
   uint64_t seed = 0;
   unsigned flags = 0;
@@ -280,7 +294,9 @@ struct WsLayout {
   size_t a_L, a_nnew, a_knew, a_tnew, a_taunew, a_ar, a_flags;
 };
 
-WsLayout ws_layout(const tppsd_model *T, const tppsd_model *D, int B, int cap, int MG) {
+// pre_rows: rows of the activation scratch that prefill chunks use (prefill_rows, or 0 for
+// what the rounds need, which is what a workspace must hold at least)
+WsLayout ws_layout(const tppsd_model *T, const tppsd_model *D, int B, int cap, int MG, size_t pre_rows) {
   WsLayout w;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -319,13 +335,14 @@ WsLayout ws_layout(const tppsd_model *T, const tppsd_model *D, int B, int cap, i
   const size_t fmax = std::max(T->cfg.d_ffn, D ? D->cfg.d_ffn : 0);
   const size_t mmax = std::max(T->cfg.n_mix, D ? D->cfg.n_mix : 0);
   const size_t kmax = std::max(T->cfg.n_types, D ? D->cfg.n_types : 0);
-  w.x = take(Tm * dmax * 4);
-  w.a = take(Tm * dmax * 4);
-  w.q = take(Tm * dmax * 4);
-  w.o = take(Tm * dmax * 4);
-  w.hid = take(Tm * fmax * 4);
+  const size_t Tp = std::max(Tm, pre_rows);   // (the decoder's e and logits: no prefill row reaches it)
+  w.x = take(Tp * dmax * 4);
+  w.a = take(Tp * dmax * 4);
+  w.q = take(Tp * dmax * 4);
+  w.o = take(Tp * dmax * 4);
+  w.hid = take(Tp * fmax * 4);
   w.e = take(Tm * 4 * dmax * 4);
-  w.u = take(Tm * 2 * dmax * 4);   // AttNHP layer input [z; h]
+  w.u = take(Tp * 2 * dmax * 4);   // AttNHP layer input [z; h]
   w.logits = take(Tm * head_ldl((int)mmax, (int)kmax) * 4);
   w.hwT = take((size_t)(3 * T->cfg.n_mix + T->cfg.n_types) * 4 * T->d() * T->act_bytes());
   w.hbT = take((size_t)(3 * T->cfg.n_mix + T->cfg.n_types) * 4);
@@ -438,6 +455,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
       e.cap = s->kv_cap;
       e.status = s->status;
       launch_gemm(s->u, nullptr, w.qkv_w, bf, T, 3 * d, 2 * d, e, st, ev(L + 4 * l, 0), ev(L + 4 * l, 1));
+      if (!head && l + 1 == L) break;   // (prefill: past the last layer's keys and values nothing is used)
       launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
                        1, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
       launch_attnhp_update(s->x, s->o, s->u, s->a, bf, T, d, st);
@@ -447,8 +465,8 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     // small THP models: one k_block launch between consecutive attention
     // launches (embedding + LN1 + QKV; then output projection + FFN + the next
     // LN1 + QKV; the last one ends with LN_f and the decoder). Without a
-    // decoder the last layer's output projection and FFN feed nothing and
-    // are skipped.
+    // decoder (prefill) the last layer's attention, output projection and FFN
+    // feed nothing and are skipped.
     const int M = m->cfg.n_mix, K = m->cfg.n_types;
     BlockArgs ba{};
     ba.T = T;
@@ -498,10 +516,10 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     launch_block(ba, bf, st, ev(L, 0), ev(L, 1));
     for (int l = 0; l < L; ++l) {
       char *kc = c.k + c.layer_bytes * l, *vc = c.v + c.layer_bytes * l;
-      launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                       0, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
       const bool last = l + 1 == L;
       if (last && !head) break;
+      launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
+                       0, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
       const LayerW &w = m->layers[l];
       ba.first = 0;
       ba.pre = 1;
@@ -560,6 +578,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
       launch_gemm(s->a, ln_gemm ? &ln1 : nullptr, w.qkv_w, bf, T, 3 * d, d, e, st, ev(L + 4 * l, 0),
                   ev(L + 4 * l, 1));
     }
+    if (!head && l + 1 == L) break;   // (prefill: past the last layer's keys and values nothing is used)
     launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
                      0, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
     if (use_layer_fused) {
@@ -1104,7 +1123,7 @@ int tppsd_state_bytes(const tppsd_model *T, const tppsd_model *D, int B, int max
     return fail(TPPSD_E_ARG, "need B >= 1, max_events >= 3, 1 <= max_gamma <= %d", TPPSD_MAX_GAMMA);
   if (D && (D->cfg.n_mix != T->cfg.n_mix || D->cfg.n_types != T->cfg.n_types))
     return fail(TPPSD_E_CONFIG, "draft and target must share n_mix and n_types");
-  *bytes = ws_layout(T, D, B, max_events, max_gamma).total;
+  *bytes = ws_layout(T, D, B, max_events, max_gamma, prefill_rows(B, max_events)).total;
   return TPPSD_OK;
 }
 
@@ -1114,9 +1133,16 @@ int tppsd_state_create(const tppsd_model *T, const tppsd_model *D, int B, int ma
   if (int rc = tppsd_state_bytes(T, D, B, max_events, max_gamma, &need)) return rc;
   if (!d_ws || !out) return fail(TPPSD_E_ARG, "null workspace or output pointer");
   if ((uintptr_t)d_ws % ALIGN) return fail(TPPSD_E_WORKSPACE, "workspace must be 256-byte aligned");
-  if (ws_bytes < need) return fail(TPPSD_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
+  // a smaller workspace that holds the rounds' scratch is taken too: prefill then runs in
+  // chunks of PREFILL_CHUNK positions
+  size_t pre_rows = prefill_rows(B, max_events);
+  if (ws_bytes < need) {
+    pre_rows = 0;
+    if (ws_bytes < ws_layout(T, D, B, max_events, max_gamma, 0).total)
+      return fail(TPPSD_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
+  }
   if (flags & ~TPPSD_FLAG_BONUS) return fail(TPPSD_E_ARG, "unknown flags 0x%x", flags);
-  const WsLayout w = ws_layout(T, D, B, max_events, max_gamma);
+  const WsLayout w = ws_layout(T, D, B, max_events, max_gamma, pre_rows);
   tppsd_state *s = new tppsd_state();
   s->T = T;
   s->D = D;
@@ -1124,7 +1150,7 @@ int tppsd_state_create(const tppsd_model *T, const tppsd_model *D, int B, int ma
   s->cap = max_events;
   s->kv_cap = kv_stride(max_events);
   s->max_gamma = max_gamma;
-  s->Pmax = std::max(max_gamma + 1, PREFILL_CHUNK);
+  s->chunk = std::max(PREFILL_CHUNK, (int)(pre_rows / B));
   s->seed = seed;
   s->flags = flags;
   char *ws = (char *)d_ws;
@@ -1364,8 +1390,8 @@ int tppsd_prefill_window(tppsd_state *s, const float *d_t, const int32_t *d_k, i
     const tppsd_model *m = which ? s->D : s->T;
     const ModelCache &c = which ? s->cD : s->cT;
     const int n_enc = n0 - 1 - which;
-    for (int c0 = 0; c0 < n_enc; c0 += PREFILL_CHUNK) {
-      const int P = std::min(PREFILL_CHUNK, n_enc - c0);
+    for (int c0 = 0; c0 < n_enc; c0 += s->chunk) {
+      const int P = std::min(s->chunk, n_enc - c0);
       TokSrc src{};
       src.ev_t = s->ev_t;
       src.ev_k = s->ev_k;

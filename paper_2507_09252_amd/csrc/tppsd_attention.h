@@ -28,6 +28,11 @@ inline size_t attn_part_floats(int B, int H, int dh, int qtiles_max, int max_key
   const int s = attn_splits(B, H, max_keys);
   return s > 1 ? (size_t)B * H * qtiles_max * 16 * s * (dh + 2) : 0;
 }
+// The split-key kernels serve the verify pass (up to three query tiles of 16
+// over the whole cache, the partials sized for them) and passes of up to this
+// many new positions per sequence; longer blocks (prefill chunks) run
+// k_attn_rows, which splits the queries instead of the keys and has no partials.
+constexpr int ATTN_ROWS_MIN_P = 16;
 // sink: AttNHP normalisation 1 + sum f (an extra key of score 0, value 0)
 void launch_attention(const void *q, const void *kc, const void *vc, void *o, int bf16,
                       const int32_t *start, int start_off, const int32_t *done, int B, int P, int H,

@@ -464,6 +464,295 @@ __global__ __launch_bounds__(256) void k_attn_mfma_f32(int H, int P, const int32
   }
 }
 
+// ---------------------------------------------------------------------------
+// Causal attention of a long block of new queries (prefill chunks): a wave
+// owns 16 QT consecutive queries of one (sequence, head) and walks every key
+// up to its last query by itself, 32 keys per step, so that nothing is merged
+// and no barrier is taken. Same products, operand layouts, rounding points
+// and masks as the split-key kernels above.
+// What bounds it: the loads of keys and values (8 KB a step at d_head 64)
+// through the L1, about 130 cycles a step against the 18 matrix products and
+// the softmax of 32 queries; they come from L2, where a (sequence, head) slab
+// of a seed history fits, so the next step's are issued before the current
+// step is computed. Two query tiles per wave halve the key traffic of one;
+// the grid puts the block's last (longest) queries first. Measured at 32
+// sequences x 8 heads x 511 queries of d_head 64: 36 us, against 32 launches
+// of k_attn_mfma over 16 queries each, 7.3 us on average.
+// ---------------------------------------------------------------------------
+template <int DH, int QT>
+__global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *__restrict__ start,
+                                                   const int32_t *__restrict__ done, int start_off,
+                                                   const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc,
+                                                   const bf16_t *__restrict__ vc, bf16_t *__restrict__ o, int cap,
+                                                   int sink) {
+  constexpr int KT = 32, NDT = DH / 16, NC = DH >= 32 ? DH / 32 : 1;
+  const int bh = blockIdx.x, b = bh / H, h = bh - b * H;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
+  const int d = H * DH;
+  const int q0 = ((gridDim.y - 1 - blockIdx.y) * 4 + wave) * 16 * QT;
+  if (q0 >= P) return;
+  const int base = start[b] + start_off;
+  const bool skip = done != nullptr && done[b] != 0;
+  const int k_end = skip ? 0 : min(base + min(q0 + 16 * QT, P), cap);   // keys of the wave's last query, within the slab
+  const size_t kvbase = ((size_t)b * H + h) * cap;
+  const float scale2 = 1.4426950408889634f / sqrtf((float)DH);   // base-2 scores, as above
+  constexpr float LN2 = 0.69314718055994531f;
+  const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+  bf16x8_t qf[QT][NC];
+  short4_t qf16[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const bf16_t *qp = q + (size_t)(b * P + min(q0 + 16 * t + rr, P - 1)) * d + h * DH;
+    if (DH >= 32) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) qf[t][c] = *(const bf16x8_t *)(qp + 32 * c + 8 * g);
+    } else {
+      qf16[t] = *(const short4_t *)(qp + 4 * g);
+    }
+  }
+  float m_run[QT];
+  f32x4_t oacc[QT][NDT], lacc[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    m_run[t] = -INFINITY;
+    lacc[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int td = 0; td < NDT; ++td) oacc[t][td] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  }
+  const int krow0 = 8 * (rr >> 2) + (rr & 3), krow1 = krow0 + 4;
+  struct Step {
+    bf16x8_t a0[NC], a1[NC];
+    short4_t b0, b1;
+    uint4 vw[NDT];
+  };
+  // (unconditional: rows past the slab and value blocks past the key range
+  // are clamped into them and masked below)
+  auto fetch = [&](Step &f, int kt) {
+    const size_t r0 = kvbase + min(kt + krow0, cap - 1), r1 = kvbase + min(kt + krow1, cap - 1);
+    if (DH >= 32) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        f.a0[c] = *(const bf16x8_t *)(kc + r0 * DH + 32 * c + 8 * g);
+        f.a1[c] = *(const bf16x8_t *)(kc + r1 * DH + 32 * c + 8 * g);
+      }
+    } else {
+      f.b0 = *(const short4_t *)(kc + r0 * DH + 4 * g);
+      f.b1 = *(const short4_t *)(kc + r1 * DH + 4 * g);
+    }
+    const int k8c = min(kt + 8 * g, (k_end - 1) & ~7);
+#pragma unroll
+    for (int td = 0; td < NDT; ++td)
+      f.vw[td] = *(const uint4 *)(vc + kvbase * DH + (size_t)(k8c >> 3) * (8 * DH) + (16 * td + rr) * 8);
+  };
+  Step cur, nxt;
+  if (k_end > 0) fetch(cur, 0);
+  for (int kt = 0; kt < k_end; kt += KT) {
+    fetch(nxt, min(kt + KT, (k_end - 1) & ~(KT - 1)));   // (the last step's again past the end, unused)
+    const bool interior = kt + KT <= base + q0 + 1 && kt + KT <= k_end;   // every key visible to every query
+    if (!interior) {
+      const int nv = k_end - (kt + 8 * g);
+      if (nv < 8) {
+#pragma unroll
+        for (int td = 0; td < NDT; ++td) {
+          uint32_t w[4] = {cur.vw[td].x, cur.vw[td].y, cur.vw[td].z, cur.vw[td].w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (2 * i >= nv) w[i] = 0u;
+            else if (2 * i + 1 >= nv) w[i] &= 0xFFFFu;
+          }
+          cur.vw[td] = (uint4){w[0], w[1], w[2], w[3]};
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+      if (DH >= 32) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a0[c], qf[t][c], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a1[c], qf[t][c], s1, 0, 0, 0);
+        }
+      } else {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur.b0, qf16[t], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur.b1, qf16[t], s1, 0, 0, 0);
+      }
+      const int my_last = base + q0 + 16 * t + rr;
+      float sv[8];
+      float mx = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int key = kt + 8 * g + j;
+        const float raw = (j < 4) ? s0[j] : s1[j - 4];
+        const bool ok = interior || (key < k_end && key <= my_last);
+        sv[j] = ok ? raw * scale2 : -INFINITY;
+        mx = fmaxf(mx, sv[j]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run[t], mx);
+      const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
+      uint32_t pw[4];
+#pragma unroll
+      for (int j = 0; j < 8; j += 2)
+        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
+      const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, (uint4){pw[0], pw[1], pw[2], pw[3]});
+      m_run[t] = m_new;
+      if (__ballot(alpha != 1.f) != 0ull) {
+        lacc[t] *= alpha;
+#pragma unroll
+        for (int td = 0; td < NDT; ++td) oacc[t][td] *= alpha;
+      }
+      lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, lacc[t], 0, 0, 0);
+#pragma unroll
+      for (int td = 0; td < NDT; ++td)
+        oacc[t][td] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur.vw[td]), pb,
+                                                              oacc[t][td], 0, 0, 0);
+    }
+    cur = nxt;
+  }
+  // lane (rr, g) holds O^T[16 td + 4 g + i][query 16 t + rr]: four consecutive columns
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int qq = q0 + 16 * t + rr;
+    if (qq >= P) continue;
+    float L = lacc[t][0], f = 1.f;
+    if (sink) {
+      const float M = m_run[t] * LN2, ms = fmaxf(M, 0.f);
+      f = (M == -INFINITY) ? 0.f : expf(M - ms);
+      L = L * f + expf(-ms);
+    }
+    const float r = L > 0.f ? f / L : 0.f;
+#pragma unroll
+    for (int td = 0; td < NDT; ++td)
+      *(uint2 *)(o + (size_t)(b * P + qq) * d + h * DH + 16 * td + 4 * g) =
+          make_uint2(pk2bf(oacc[t][td][0] * r, oacc[t][td][1] * r), pk2bf(oacc[t][td][2] * r, oacc[t][td][3] * r));
+  }
+}
+
+// The same for fp32 caches (the products of k_attn_mfma_f32, one 32-key step
+// at a time, the next step's keys and values in flight).
+template <int DH, int QT>
+__global__ __launch_bounds__(256) void k_attn_rows_f32(int H, int P, const int32_t *__restrict__ start,
+                                                       const int32_t *__restrict__ done, int start_off,
+                                                       const float *__restrict__ q, const float *__restrict__ kc,
+                                                       const float *__restrict__ vc, float *__restrict__ o, int cap,
+                                                       int sink) {
+  constexpr int KT = 32, NDT = DH / 16;
+  const int bh = blockIdx.x, b = bh / H, h = bh - b * H;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
+  const int d = H * DH;
+  const int q0 = ((gridDim.y - 1 - blockIdx.y) * 4 + wave) * 16 * QT;
+  if (q0 >= P) return;
+  const int base = start[b] + start_off;
+  const bool skip = done != nullptr && done[b] != 0;
+  const int k_end = skip ? 0 : min(base + min(q0 + 16 * QT, P), cap);
+  const size_t kvbase = ((size_t)b * H + h) * cap;
+  const float scale = 1.f / sqrtf((float)DH);
+  f32x4_t qf[QT][NDT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const float *qp = q + (size_t)(b * P + min(q0 + 16 * t + rr, P - 1)) * d + h * DH;
+#pragma unroll
+    for (int c = 0; c < NDT; ++c) qf[t][c] = *(const f32x4_t *)(qp + 16 * c + 4 * g);
+  }
+  float m_run[QT], l_run[QT];
+  f32x4_t oacc[QT][NDT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    m_run[t] = -INFINITY;
+    l_run[t] = 0.f;
+#pragma unroll
+    for (int td = 0; td < NDT; ++td) oacc[t][td] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  }
+  const int krow0 = 8 * (rr >> 2) + (rr & 3), krow1 = krow0 + 4;
+  struct Step {
+    f32x4_t a0[NDT], a1[NDT];
+    float vv[NDT][8];
+  };
+  auto fetch = [&](Step &f, int kt) {
+    const size_t r0 = kvbase + min(kt + krow0, cap - 1), r1 = kvbase + min(kt + krow1, cap - 1);
+#pragma unroll
+    for (int c = 0; c < NDT; ++c) {
+      f.a0[c] = *(const f32x4_t *)(kc + r0 * DH + 16 * c + 4 * g);
+      f.a1[c] = *(const f32x4_t *)(kc + r1 * DH + 16 * c + 4 * g);
+    }
+#pragma unroll
+    for (int td = 0; td < NDT; ++td)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        f.vv[td][j] = vc[(kvbase + min(kt + 8 * g + j, k_end - 1)) * DH + 16 * td + rr];
+  };
+  Step cur, nxt;
+  if (k_end > 0) fetch(cur, 0);
+  for (int kt = 0; kt < k_end; kt += KT) {
+    fetch(nxt, min(kt + KT, (k_end - 1) & ~(KT - 1)));
+    // (keys past the range carry probability 0 and a finite clamped value)
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < NDT; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.a0[c][e], qf[t][c][e], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.a1[c][e], qf[t][c][e], s1, 0, 0, 0);
+        }
+      const int my_last = base + q0 + 16 * t + rr;
+      float sv[8];
+      float mx = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int key = kt + 8 * g + j;
+        const float raw = (j < 4) ? s0[j] : s1[j - 4];
+        sv[j] = (key < k_end && key <= my_last) ? raw * scale : -INFINITY;
+        mx = fmaxf(mx, sv[j]);
+      }
+      mx = fmaxf(mx, swz_xor<16>(mx));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run[t], mx);
+      const float alpha = (m_new == -INFINITY) ? 1.f : expf(m_run[t] - m_new);
+      float ps = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        sv[j] = (sv[j] == -INFINITY) ? 0.f : expf(sv[j] - m_new);
+        ps += sv[j];
+      }
+      ps += swz_xor<16>(ps);
+      ps += __shfl_xor(ps, 32, 64);
+      l_run[t] = l_run[t] * alpha + ps;
+      m_run[t] = m_new;
+#pragma unroll
+      for (int td = 0; td < NDT; ++td) {
+        oacc[t][td] *= alpha;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          oacc[t][td] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.vv[td][j], sv[j], oacc[t][td], 0, 0, 0);
+      }
+    }
+    cur = nxt;
+  }
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int qq = q0 + 16 * t + rr;
+    if (qq >= P) continue;
+    float L = l_run[t], f = 1.f;
+    if (sink) {
+      const float M = m_run[t], ms = fmaxf(M, 0.f);
+      f = (M == -INFINITY) ? 0.f : expf(M - ms);
+      L = L * f + expf(-ms);
+    }
+#pragma unroll
+    for (int td = 0; td < NDT; ++td) {
+      f32x4_t v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = L > 0.f ? oacc[t][td][i] * f / L : 0.f;
+      *(f32x4_t *)(o + (size_t)(b * P + qq) * d + h * DH + 16 * td + 4 * g) = v;
+    }
+  }
+}
+
 // merge of the split partials: one thread per output element
 template <typename ACT, int DH>
 __global__ void k_attn_combine(const float *__restrict__ part, ACT *__restrict__ o, int total, int P, int H,
@@ -495,6 +784,22 @@ template <typename ACT, int DH, int ROLE>
 static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const int32_t *start, int start_off,
                       const int32_t *done, int B, int P, int H, int cap, float *part, int sink, hipEvent_t ev0,
                       hipEvent_t ev1, hipStream_t s) {
+  if (ROLE == 0 && P > ATTN_ROWS_MIN_P) {
+    // a prefill chunk: waves of 32 queries (16 while that leaves compute units idle)
+    auto rows = [&](auto kern, int per_wg) {
+      hipExtLaunchKernelGGL(kern, dim3(B * H, (P + per_wg - 1) / per_wg), dim3(256), 0, s, ev0, ev1, 0, H, P, start,
+                            done, start_off, Q, Kc, Vc, O, cap, sink);
+    };
+    const bool two = (long)B * H * ((P + 127) / 128) >= 256;
+    if constexpr (sizeof(ACT) == 2) {
+      if (two) rows(k_attn_rows<DH, 2>, 128);
+      else rows(k_attn_rows<DH, 1>, 64);
+    } else {
+      if (two) rows(k_attn_rows_f32<DH, 2>, 128);
+      else rows(k_attn_rows_f32<DH, 1>, 64);
+    }
+    return;
+  }
   const int qtiles = (P + 15) / 16;
   int splits = attn_splits(B, H, cap);
   // bf16: two splits of four waves become one workgroup of eight

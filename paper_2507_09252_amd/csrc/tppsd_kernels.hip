@@ -1182,6 +1182,128 @@ __global__ __launch_bounds__(256) void k_gemm_dl(const bf16_t *__restrict__ X, c
 }
 
 // ---------------------------------------------------------------------------
+// bf16 GEMM for many rows (prefill chunks of thousands of rows): a workgroup
+// of 4 waves (2 x 2) owns a BM x BN output tile, each wave (BM / 2) x (BN / 2)
+// of it in 16 x 16 MFMA tiles, over stages of 64 k moved straight into LDS.
+// What bounds it: the matrix units once the tile is large enough that a
+// stage's LDS reads (one 16-byte fragment per 16 rows and 32 k) are shared by
+// BM / 32 resp. BN / 32 products. Two ring slots (64 KB) leave room for two
+// workgroups per CU, whose barriers and epilogues overlap each other's
+// products. Chunk c of tile row r is stored at chunk c ^ ((r / 2) mod 8), so
+// that the 16 rows of a fragment read cover all 64 banks once.
+// Workgroups go round robin over the 8 XCDs: XCD x takes the x-th eighth of
+// the tiles in row-major order, so that a block of rows is read into one L2
+// only and the matrix, which every row block needs, stays in each.
+// Measured at 16352 rows: N = 2048, K = 512 55 us (620 TFLOP/s); the same
+// rows in 32 chunks of 512 through k_gemm_dl took 32 x 7.6 us.
+// ---------------------------------------------------------------------------
+template <int BM, int BN>
+__global__ __launch_bounds__(256) void k_gemm_tall(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W, int T,
+                                                   int N, int K, Epi e) {
+  constexpr int KSN = 2, BK = 32 * KSN, CPR = BK / 8, TM = BM / 32, TN = BN / 32;
+  constexpr int ACH = BM * CPR, BCH = BN * CPR, NIA = ACH / 256, NIB = BCH / 256, STAGE = (ACH + BCH) * 16;
+  constexpr int CLD = BN + 4;
+  constexpr int CBYTES = BM * CLD * 4, SMEM = 2 * STAGE > CBYTES ? 2 * STAGE : CBYTES;
+  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rr = lane & 15, g = lane >> 4;
+  const int ntn = N / BN, total = ntn * ((T + BM - 1) / BM), per = (total + 7) / 8;
+  const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if (tile >= total) return;
+  const int m0 = tile / ntn * BM, n0 = tile % ntn * BN;
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+  auto chunk = [](int row, int c) { return row * CPR + (c ^ ((row >> 1) & (CPR - 1))); };
+  const bf16_t *srcA[NIA], *srcB[NIB];
+#pragma unroll
+  for (int i = 0; i < NIA; ++i) {
+    const int p = (4 * i + wave) * 64 + lane, row = p / CPR, c = (p % CPR) ^ ((row >> 1) & (CPR - 1));
+    srcA[i] = X + (size_t)min(m0 + row, T - 1) * K + 8 * c;   // (rows past T are never stored)
+  }
+#pragma unroll
+  for (int i = 0; i < NIB; ++i) {
+    const int p = (4 * i + wave) * 64 + lane, row = p / CPR, c = (p % CPR) ^ ((row >> 1) & (CPR - 1));
+    srcB[i] = W + (size_t)(n0 + row) * K + 8 * c;
+  }
+  f32x4_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  auto issue = [&](char *base, int st) {
+#pragma unroll
+    for (int i = 0; i < NIA; ++i)
+      __builtin_amdgcn_global_load_lds((const void *)(srcA[i] + st * BK), (lds_ptr_t)(base + (4 * i + wave) * 1024), 16,
+                                       0, 0);
+#pragma unroll
+    for (int i = 0; i < NIB; ++i)
+      __builtin_amdgcn_global_load_lds((const void *)(srcB[i] + st * BK),
+                                       (lds_ptr_t)(base + ACH * 16 + (4 * i + wave) * 1024), 16, 0, 0);
+  };
+  const int nst = K / BK;
+  issue(smem, 0);
+  for (int st = 0; st < nst; ++st) {
+    wait_vmcnt<0>();                 // this wave's part of stage st has landed
+    __builtin_amdgcn_s_barrier();    // everyone's; and nobody reads the other slot any more
+    const char *As = smem + (st & 1) * STAGE, *Bs = As + ACH * 16;
+    bf16x8_t a[KSN][TM], b[KSN][TN];
+#pragma unroll
+    for (int ks = 0; ks < KSN; ++ks) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[ks][i] = *(const bf16x8_t *)(As + chunk(wm + 16 * i + rr, 4 * ks + g) * 16);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[ks][j] = *(const bf16x8_t *)(Bs + chunk(wn + 16 * j + rr, 4 * ks + g) * 16);
+    }
+    // the next stage goes out once this one's fragments are read, so that the
+    // compiler, which cannot tell the slots apart, has no load in flight to
+    // wait for before those reads
+    if (st + 1 < nst) issue(smem + ((st + 1) & 1) * STAGE, st + 1);
+#pragma unroll
+    for (int ks = 0; ks < KSN; ++ks)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+  }
+  // through LDS (over the ring) to 8 consecutive columns per thread
+  __syncthreads();
+  float *Cs = (float *)smem;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Cs[(wm + 16 * i + 4 * g + v) * CLD + wn + 16 * j + rr] = acc[i][j][v];
+  __syncthreads();
+  if (e.mode == EPI_QKV && n0 >= 2 * e.d) {
+    // a tile of values: lanes over 8 rows x 8 columns, whose elements of the
+    // position-blocked cache are 128 contiguous bytes (row by row they would
+    // be single elements 16 bytes apart)
+    for (int i = tid; i < BM * BN; i += 256) {
+      const int col = (i >> 3) % BN, row = (i & 7) + 8 * ((i >> 3) / BN);
+      const int r = m0 + row, c = n0 + col - 2 * e.d;
+      if (r >= T) continue;
+      const int b = r / e.P, pos = e.start[b] + e.start_off + (r - b * e.P);
+      if (pos < e.cap)
+        st((bf16_t *)e.vc, v_at<bf16_t>(((size_t)b * e.H + c / e.dh) * e.cap, pos, c % e.dh, e.dh),
+           Cs[row * CLD + col] + e.bias[n0 + col]);
+      else
+        atomicOr(e.status, TPPSD_STATUS_CAPACITY);
+    }
+    return;
+  }
+  for (int i = tid; i < BM * (BN / 8); i += 256) {
+    const int row = i / (BN / 8), c8 = i % (BN / 8);
+    const int r = m0 + row, n = n0 + 8 * c8;
+    if (r >= T) continue;
+    float cv[8];
+    Epi8In in;
+    epilogue8_fetch(e, r, n, in);
+    load8f(Cs + row * CLD + 8 * c8, cv);
+    epilogue8<bf16_t>(e, r, n, cv, in);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // decoder (§4.2): the mixture parameters (V_w e1, V_mu e2, V_sigma e3) and
 // the type logits (V_k2 tanh(V_k1 h + b1)) of a row are one product of the
 // concatenated [e1 e2 e3 tanh(.)] (4d wide) with a block-diagonal
@@ -3696,6 +3818,17 @@ static void gemm_dispatch(const void *X, const LnA *ln, const void *W, int T, in
     hipExtLaunchKernelGGL(kern, grid, dim3(256), 0, s, ev0, ev1, 0, x, xf, lg, lb, w, T, N, K, epi);
   };
   if (!ln) {
+    // bf16, enough rows that 128 x 128 tiles fill the chip (a value tile of
+    // q, k, v must not straddle the keys): the tall GEMM. Below one tile per CU
+    // the smaller tiles spread the latency (4064 rows, 128 tiles of N = 512:
+    // k_gemm_dl 20.7 us, K = 512 and 2048)
+    if (sizeof(ELT) == 2 && N % 128 == 0 && K % 64 == 0 && (epi.mode != EPI_QKV || epi.d % 128 == 0) &&
+        (long)(N / 128) * ((T + 127) / 128) >= 256) {
+      const int tiles = (N / 128) * ((T + 127) / 128);
+      hipExtLaunchKernelGGL((k_gemm_tall<128, 128>), dim3((tiles + 7) / 8 * 8), dim3(256), 0, s, ev0, ev1, 0,
+                            (const bf16_t *)X, (const bf16_t *)W, T, N, K, epi);
+      return;
+    }
     // bf16, a few hundred 64 x 64 tiles or fewer over at least 512 rows, K a
     // multiple of 128: direct-to-LDS ring of 32 x 32 x 128 stages (measured
     // faster there; the register ring keeps the very tall GEMMs)

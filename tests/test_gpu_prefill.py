@@ -1,0 +1,99 @@
+"""Prefill in long chunks against the oracle: the verify pass that follows an
+encoded history reads every key and value the prefill wrote, so its outputs
+(decoder rows and log-densities at given drafts) are compared, at sizes around
+the edges of the prefill kernels' tiles. Tolerances: the fixed per-workload
+bounds of gpu_common (float32 1e-5; bf16 2e-3, or 4e-3 at d = 512)."""
+import ctypes
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import (Case, check_verify, draft_buffers_from_oracle, f32_round, gpu_state, histories, small, to_dev,
+                        tol_of, verify_out, weights)
+from oracle import sampler as S
+from oracle.model import Model as OModel
+from paper_2507_09252_amd import tppsd as tp
+from paper_2507_09252_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# a target wide enough for the 128 x 128-tile GEMM (q, k, v tiles of keys and
+# values, FFN and output tiles of four and more per row block), two layers
+WIDE = dataclasses.replace(W.WORKLOADS["c4"], target=W.ModelCfg(2, 512, 8, 512, 4, 3, "bf16"),
+                           draft=W.ModelCfg(1, 64, 4, 64, 4, 3, "bf16"), gammas=(3,))
+NHP = dataclasses.replace(W.WORKLOADS["c1"], target=W.ModelCfg(2, 32, 2, 0, 4, 3, "fp32", "attnhp", 0.1, 50.0),
+                          draft=W.ModelCfg(1, 16, 1, 0, 4, 3, "fp32", "attnhp", 0.1, 50.0), history="hawkes5")
+CASES = (
+    # one chunk of n_hist - 1 positions around the edges of a wave's 16 or 32
+    # queries and a step's 32 keys: d_head 16 (fp32), 32 and 64 (bf16)
+    [small(n, 3, n_hist=h, init="bias") for n in ("c2", "c3") for h in (17, 18, 33, 34, 66, 130)] +
+    [small("c4", 2, n_hist=h, init="bias") for h in (18, 67)] +
+    # enough (sequence, head, query block) items for two query tiles per wave
+    [small("c2", 40, n_hist=140, init="bias"), small("c3", 20, n_hist=140, init="bias")] +
+    # AttNHP (the extra key of score 0), bf16 and fp32
+    [small("a3", 3, n_hist=100, init="bias"), Case("nhp-fp32", NHP, 3, 75, "bias", True)] +
+    # several chunks (48 positions of 300 sequences, then 48, then 3)
+    [small("c5", 300, n_hist=100, init="bias")] +
+    # 8256 rows of width 512, the last row block ragged; and 8320, a whole number
+    [Case("wide-B64-h130", WIDE, 64, 130, "bias", True), Case("wide-B64-h131", WIDE, 64, 131, "bias", True)])
+
+
+def _verify(case, st, dr, ht, hk, n_gen):
+    M, K = case.wl.target.n_mix, case.wl.target.n_types
+    st.tppsd_prefill(to_dev(ht), to_dev(hk), n_gen)
+    vbuf = tp.VerifyBuffers(case.B, case.g, M, K)
+    st.tppsd_verify(case.g, draft_buffers_from_oracle(dr, case.B, case.g, M, K), vbuf)
+    torch.cuda.synchronize()
+    assert st.tppsd_state_status()["bits"] == 0
+    return verify_out(vbuf, np.arange(case.B), case.g)
+
+
+def _drafts(case, ht, seed):
+    """Any drafts will do: log-normal intervals, uniform types."""
+    rng = np.random.default_rng(seed)
+    B, g, M, K = case.B, case.g, case.wl.target.n_mix, case.wl.target.n_types
+    tau = np.exp(0.5 * rng.normal(size=(B, g))).astype(np.float32)
+    t = (ht[:, -1:].astype(np.float64) + np.cumsum(tau, 1)).astype(np.float32).astype(np.float64)
+    z = np.zeros((B, g, M))
+    return S.DraftOut(tau=tau.astype(np.float64), t=t, k=rng.integers(0, K, size=(B, g)), logg=np.zeros((B, g)),
+                      logf=np.zeros((B, g)), logw=z, mu=z, s=z, logtype=np.zeros((B, g, K)),
+                      cat_margin=np.zeros((B, g)))
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c.name for c in CASES])
+def test_verify_after_long_prefill(case):
+    wt, wd = weights(case)
+    ht, hk = histories(case)
+    hk = hk % case.wl.target.n_types
+    print(f"{case.name}: B {case.B}, history {case.n_hist}, gamma {case.g}", flush=True)
+    dr = _drafts(case, ht, 5)
+    T = OModel(case.wl.target, wt)
+    want = S.verify(T, S.prefill(T, None, ht, hk, 8), dr, np.arange(case.B))
+    got = _verify(case, gpu_state(case, wt, wd, case.g, 8, 3), dr, ht, hk, 8)
+    tol = tol_of(case.wl)
+    check_verify(got, want, tol, case.name, False, dr)
+
+
+@pytest.mark.parametrize("case", [small("c2", 5, n_hist=90, init="bias"), small("c3", 5, n_hist=90, init="bias")],
+                         ids=["c2", "c3"])
+def test_smaller_workspace_prefills_in_short_chunks(case):
+    # one byte less than tppsd_state_bytes asks for still holds the rounds'
+    # scratch: accepted, and the same results from chunks of 16 positions
+    wt, wd = weights(case)
+    ht, hk = histories(case)
+    dr = _drafts(case, ht, 6)
+    st = gpu_state(case, wt, wd, case.g, 8, 3)
+    want = _verify(case, st, dr, ht, hk, 8)
+    L, n, h = tp.lib(), ctypes.c_size_t(), ctypes.c_void_p()
+    args = (st.target.handle, st.draft.handle, st.B, st.max_events, st.max_gamma)
+    assert L.tppsd_state_bytes(*args, ctypes.byref(n)) == 0
+    ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
+    assert L.tppsd_state_create(*args, 3, tp.FLAG_BONUS, ws.data_ptr(), n.value - 1, ctypes.byref(h)) == 0
+    L.tppsd_state_destroy(st.handle)
+    st.handle, st.ws = h, ws
+    got = _verify(case, st, dr, ht, hk, 8)
+    tol = tol_of(case.wl)
+    for f in ("logw", "mu", "s", "logtype"):
+        assert np.abs(getattr(got, f) - getattr(want, f)).max() <= tol, f
