@@ -70,6 +70,26 @@ template <int XOR> __device__ __forceinline__ float swz_xor(float v) {
   static_assert(XOR < 32, "swizzle reaches 32 lanes");
   return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), (XOR << 10) | 0x1F));
 }
+// the value of lane ^ 16 / lane ^ 32 combined with this lane's own, by gfx950's
+// row and half-wave swaps (vector-ALU moves; a bpermute goes through the LDS
+// pipe): swapping v with itself leaves the two partners of a pair in the two
+// results of both lanes
+__device__ __forceinline__ float xor16_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float xor32_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float xor16_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float xor32_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 // sum / max over aligned groups of `width` lanes (a power of two <= 64),
 // left in every lane of the group
 __device__ __forceinline__ float group_sum(float v, int width) {

@@ -427,6 +427,56 @@ __device__ __forceinline__ void epilogue8(const Epi &e, int r, int n, const floa
   }
 }
 
+// One column of an epilogue with its operands that do not depend on the
+// product fetched ahead (bias, the residual's element, the row's cache position).
+__device__ __forceinline__ void epilogue_fetch(const Epi &e, int r, int n, float &bias, float &res, int &pos) {
+  // (loads under uniform conditions only: one under a lane condition makes
+  // the compiler wait for every load before it)
+  if (e.bias) bias = e.bias[e.mode == EPI_HEAD ? max(n - e.split, 0) : n];
+  if (e.mode == EPI_RESID) res = ((const float *)e.out)[(size_t)r * e.ldo + n];
+  if (e.mode == EPI_QKV) {
+    const int b = r / e.P;
+    pos = e.start[b] + e.start_off + (r - b * e.P);
+  }
+}
+template <typename ACT>
+__device__ __forceinline__ void epilogue1(const Epi &e, int r, int n, float acc, float bias, float res, int pos) {
+  switch (e.mode) {
+    case EPI_STORE:
+      st((ACT *)e.out, (size_t)r * e.ldo + n, acc + bias);
+      break;
+    case EPI_F32:
+      ((float *)e.out)[(size_t)r * e.ldo + n] = acc + bias;
+      break;
+    case EPI_RESID:
+      ((float *)e.out)[(size_t)r * e.ldo + n] = res + (acc + bias);
+      break;
+    case EPI_RELU:
+      st((ACT *)e.out, (size_t)r * e.ldo + n, fmaxf(acc + bias, 0.f));
+      break;
+    case EPI_HEAD:
+      st((ACT *)e.out, (size_t)r * e.ldo + n, n < e.split ? acc : tanhf(acc + bias));
+      break;
+    case EPI_QKV: {
+      const float v = acc + bias;
+      const int which = n / e.d, c = n - which * e.d;
+      if (which == 0) {
+        st((ACT *)e.q, (size_t)r * e.d + c, v);
+      } else if (pos < e.cap) {
+        const int b = r / e.P, h = c / e.dh, j = c - h * e.dh;
+        const size_t row0 = ((size_t)b * e.H + h) * e.cap;
+        if (which == 1)
+          st((ACT *)e.kc, (row0 + pos) * e.dh + j, v);
+        else
+          st((ACT *)e.vc, v_at<ACT>(row0, pos, j, e.dh), v);
+      } else {
+        atomicOr(e.status, TPPSD_STATUS_CAPACITY);
+      }
+      break;
+    }
+  }
+}
+
 // One k step of an MFMA tile product with fp32 accumulation: for every 16x16
 // tile lane l holds row (l mod 16) of A and of W (W is stored [N, K], so its
 // rows are B's columns) over one slice of the k range; the accumulator holds
@@ -1179,6 +1229,123 @@ __global__ __launch_bounds__(256) void k_gemm_dl(const bf16_t *__restrict__ X, c
       for (int i = 0; i < N - n; ++i) epilogue<bf16_t>(e, r, n + i, cv[i]);
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// GEMM for few rows (AR steps, per-step drafting, small verify passes): a
+// workgroup owns 16 rows x 16 columns and its NW waves split K, NS MFMA
+// k-steps each (K = NW NS KSTEP), so that a product is one batch of loads
+// straight into operand registers, NS matrix instructions, one exchange of
+// the waves' partial sums through LDS and the epilogue.
+// What bounds it: latency. The products of a 32-row pass move a few hundred
+// KB; a tile walked stage by stage through LDS pays a barrier and an LDS
+// round trip per stage, and 32 x 32 tiles leave most CUs idle (N = 512: 16
+// workgroups). The order of the waves' sums is fixed. Measured at 32 rows
+// against the tile walked in stages: N = 512, K = 512 4.1 us and K = 2048 6.3
+// (6.8 on average); with a LayerNorm operand, K = 512, N = 1536 5.6 vs 8.0 and
+// N = 2048 5.1 vs 7.8; the decoder heads (53 columns, K = 2048) 5.8 vs 9.6.
+// LN: the A operand is LayerNorm(x) of the fp32 stream x, normalised in the
+// operand registers; each wave's share of a row's sum, then of its squared
+// deviations (two passes over the registers), goes through LDS.
+// ---------------------------------------------------------------------------
+template <typename ELT, int NW, int NS, bool LN>
+__global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X, const float *__restrict__ xf,
+                                                       const float *__restrict__ lg, const float *__restrict__ lb,
+                                                       const ELT *__restrict__ W, int T, int N, int K, Epi e) {
+  typedef MfmaStep<ELT> S;
+  constexpr int KS = S::KSTEP, VE = 16 / sizeof(ELT), LD = 20;
+  __shared__ __attribute__((aligned(16))) float red[NW][16 * LD];
+  __shared__ __attribute__((aligned(16))) float st1[LN ? 16 * NW : 4], st2[LN ? 16 * NW : 4];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rr = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  const int k0 = wave * NS * KS + VE * g;
+  // (rows past T and columns past N are clamped; their results are not stored)
+  const size_t xoff = (size_t)min(m0 + rr, T - 1) * K + k0, woff = (size_t)min(n0 + rr, N - 1) * K + k0;
+  uint4 a[NS], b[NS];
+  float4 xv[LN ? NS : 1][VE / 4], gv[LN ? NS : 1][VE / 4], bv[LN ? NS : 1][VE / 4];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (LN) {
+#pragma unroll
+      for (int c = 0; c < VE / 4; ++c) xv[s][c] = *(const float4 *)(xf + xoff + s * KS + 4 * c);
+    } else {
+      a[s] = *(const uint4 *)(X + xoff + s * KS);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < NS; ++s) b[s] = *(const uint4 *)(W + woff + s * KS);
+  if (LN) {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int c = 0; c < VE / 4; ++c) {
+        gv[s][c] = *(const float4 *)(lg + k0 + s * KS + 4 * c);
+        bv[s][c] = *(const float4 *)(lb + k0 + s * KS + 4 * c);
+      }
+  }
+  // this thread's output (the first 256 threads): row tid / 16, column tid % 16
+  const int r = m0 + (tid >> 4), n = n0 + (tid & 15);
+  float ebias = 0.f, eres = 0.f;
+  int epos = 0;
+  epilogue_fetch(e, min(r, T - 1), min(n, N - 1), ebias, eres, epos);
+  if (LN) {
+    float s1 = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int c = 0; c < VE / 4; ++c) s1 += (xv[s][c].x + xv[s][c].y) + (xv[s][c].z + xv[s][c].w);
+    s1 = xor32_sum(xor16_sum(s1));
+    if (g == 0) st1[rr * NW + wave] = s1;
+    lds_barrier();
+    float mean = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mean += st1[rr * NW + w];
+    mean /= (float)K;
+    float s2 = 0.f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int c = 0; c < VE / 4; ++c) {
+        const float4 v = xv[s][c];
+        const float c0 = v.x - mean, c1 = v.y - mean, c2 = v.z - mean, c3 = v.w - mean;
+        s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
+      }
+    s2 = xor32_sum(xor16_sum(s2));
+    if (g == 0) st2[rr * NW + wave] = s2;
+    lds_barrier();
+    float var = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) var += st2[rr * NW + w];
+    const float rstd = 1.f / sqrtf(var / (float)K + 1e-5f);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      float y[VE];
+#pragma unroll
+      for (int c = 0; c < VE / 4; ++c) {
+        const float4 v = xv[s][c], gg = gv[s][c], bb = bv[s][c];
+        y[4 * c + 0] = (v.x - mean) * rstd * gg.x + bb.x;
+        y[4 * c + 1] = (v.y - mean) * rstd * gg.y + bb.y;
+        y[4 * c + 2] = (v.z - mean) * rstd * gg.z + bb.z;
+        y[4 * c + 3] = (v.w - mean) * rstd * gg.w + bb.w;
+      }
+      if constexpr (sizeof(ELT) == 2)
+        a[s] = make_uint4(pk2bf(y[0], y[1]), pk2bf(y[2], y[3]), pk2bf(y[4], y[5]), pk2bf(y[6], y[7]));
+      else
+        a[s] = make_uint4(__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3]));
+    }
+  }
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    acc = S::mma(__builtin_bit_cast(typename S::frag, a[s]), __builtin_bit_cast(typename S::frag, b[s]), acc);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[wave][(4 * g + v) * LD + rr] = acc[v];
+  lds_barrier();
+  if (tid >= 256 || r >= T || n >= N) return;
+  float y = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) y += red[w][(tid >> 4) * LD + (tid & 15)];
+  epilogue1<ELT>(e, r, n, y, ebias, eres, epos);
 }
 
 // ---------------------------------------------------------------------------
@@ -3810,6 +3977,34 @@ static void gemm_dispatch(const void *X, const LnA *ln, const void *W, int T, in
                           hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const ELT *x = (const ELT *)X, *w = (const ELT *)W;
   const float *xf = ln ? ln->x : nullptr, *lg = ln ? ln->g : nullptr, *lb = ln ? ln->b : nullptr;
+  // few rows, K a power of two of the k-steps that have an instance: 16 x 16
+  // tiles with K split over the waves. What a CU takes in bounds it (48 KB a
+  // tile at K = 512), so the rule is on the rows. Measured, one AR step, this
+  // kernel against the 32 x 32 tiles below: d = 512 (8 layers) 32 rows 223 vs
+  // 321 us, 128 rows 413 vs 438, 256 rows 696 vs 609; d = 256 (6 layers) 32
+  // rows 128 vs 167, 256 rows 261 vs 273, 272 rows (verify) 186 vs 170; fp32
+  // d = 64 (4 layers) 256 rows 121 vs 142. (32 x 32 tiles with K split the
+  // same way take in as much per CU over fewer CUs: 32 rows 306 us.)
+  const int ksteps = K % MfmaStep<ELT>::KSTEP ? 0 : K / MfmaStep<ELT>::KSTEP;
+  if ((T <= 128 || (T <= 256 && K <= 256)) &&
+      (ksteps == 4 || ksteps == 8 || ksteps == 16 || (!ln && (ksteps == 32 || ksteps == 64)))) {
+    auto rows = [&](auto kern, int nw) {
+      hipExtLaunchKernelGGL(kern, dim3((N + 15) / 16, (T + 15) / 16), dim3(64 * nw), 0, s, ev0, ev1, 0, x, xf, lg, lb,
+                            w, T, N, K, epi);
+    };
+    if (ln) {
+      if (ksteps == 4) rows(k_gemm_rows<ELT, 4, 1, true>, 4);
+      else if (ksteps == 8) rows(k_gemm_rows<ELT, 8, 1, true>, 8);
+      else rows(k_gemm_rows<ELT, 8, 2, true>, 8);
+    } else {
+      if (ksteps == 4) rows(k_gemm_rows<ELT, 4, 1, false>, 4);
+      else if (ksteps == 8) rows(k_gemm_rows<ELT, 8, 1, false>, 8);
+      else if (ksteps == 16) rows(k_gemm_rows<ELT, 8, 2, false>, 8);
+      else if (ksteps == 32) rows(k_gemm_rows<ELT, 8, 4, false>, 8);
+      else rows(k_gemm_rows<ELT, 8, 8, false>, 8);
+    }
+    return;
+  }
   // 64 x 64 tiles when they give the chip a few hundred workgroups, 32 x 32
   // otherwise (the B rows of draft and AR steps)
   const bool big = (long)((N + 63) / 64) * ((T + 63) / 64) >= 256;
