@@ -35,7 +35,7 @@ HIPCC_FLAGS = [
 # first loads need no kernel-argument load.
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 FILE_FLAGS = {"tppsd_draft_rows.hip": PRELOAD, "tppsd_kernels.hip": PRELOAD, "tppsd_attention.hip": PRELOAD,
-              "tppsd_poisson.hip": PRELOAD}
+              "tppsd_poisson.hip": PRELOAD, "tppsd_draft_regs.hip": PRELOAD}
 
 
 def source_flags(src: str) -> list:
@@ -67,7 +67,8 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     from concurrent.futures import ThreadPoolExecutor
-    srcs = ("tppsd_kernels.hip", "tppsd_attention.hip", "tppsd_poisson.hip", "tppsd_draft_rows.hip", "tppsd.cpp")
+    srcs = ("tppsd_kernels.hip", "tppsd_attention.hip", "tppsd_poisson.hip", "tppsd_draft_rows.hip",
+            "tppsd_draft_regs.hip", "tppsd.cpp")
     objs = [os.path.join(BUILD, src + ".o") for src in srcs]
     cmds = [[hipcc] + source_flags(src) + inc + ["-x", "hip", "-c", os.path.join(CSRC, src), "-o", obj]
             for src, obj in zip(srcs, objs)]
@@ -89,7 +90,8 @@ def build_host_sanitized(out_dir: str, verbose: bool = False) -> str:
     tests of the host-side paths. Load it with the sanitizer runtime
     preloaded (sanitizer_runtime())."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
-    dev = ("tppsd_kernels.hip", "tppsd_attention.hip", "tppsd_poisson.hip", "tppsd_draft_rows.hip")
+    dev = ("tppsd_kernels.hip", "tppsd_attention.hip", "tppsd_poisson.hip", "tppsd_draft_rows.hip",
+           "tppsd_draft_regs.hip")
     objs = [os.path.join(BUILD, src + ".o") for src in dev]
     if not all(os.path.exists(o) for o in objs):
         build(verbose)

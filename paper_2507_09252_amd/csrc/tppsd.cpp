@@ -263,6 +263,7 @@ struct tppsd_state {
   bool fused_draft = true;   // one-launch drafting when the draft model fits it
   bool wave_draft = false;   // ... with one wave per sequence (small draft models)
   bool fused_w_lds = false;  // ... with its weight matrices staged in LDS
+  bool regs_draft = false;   // one-launch drafting, the model in registers (small draft models)
   bool row_draft = false;    // split attention + row workgroups per sequence, per step and layer
   hipGraphExec_t sd_exec[2] = {nullptr, nullptr};
   long long sd_key = -1;
@@ -744,7 +745,10 @@ int do_draft_fused(tppsd_state *s, int gamma, const tppsd_draft_buf *out, hipStr
   const int dp = 5 * s->T->cfg.n_layers + 1;
   const bool timed = s->cur_ev != nullptr;
   if (timed) s->ev_used[dp] = 1;
-  if (s->wave_draft)
+  if (s->regs_draft)
+    launch_draft_regs(a, D->attnhp(), D->bf16(), st, timed ? s->cur_ev[2 * dp] : nullptr,
+                      timed ? s->cur_ev[2 * dp + 1] : nullptr);
+  else if (s->wave_draft)
     launch_draft_wave(a, D->bf16(), st, timed ? s->cur_ev[2 * dp] : nullptr, timed ? s->cur_ev[2 * dp + 1] : nullptr);
   else
     launch_draft_fused(a, D->bf16(), st, timed ? s->cur_ev[2 * dp] : nullptr,
@@ -775,7 +779,7 @@ int do_draft_rows(tppsd_state *s, int gamma, const tppsd_draft_buf *out, hipStre
 
 int do_draft(tppsd_state *s, int gamma, const tppsd_draft_buf *out, hipStream_t st) {
   const tppsd_model *D = s->D;
-  if (s->wave_draft || s->fused_draft) return do_draft_fused(s, gamma, out, st);
+  if (s->regs_draft || s->wave_draft || s->fused_draft) return do_draft_fused(s, gamma, out, st);
   if (s->row_draft) return do_draft_rows(s, gamma, out, st);
   for (int l = 1; l <= gamma; ++l) {
     TokSrc src{};
@@ -1262,22 +1266,38 @@ int tppsd_state_create(const tppsd_model *T, const tppsd_model *D, int B, int ma
       s->fused_w_lds = false;       // weights stay in global memory
       (void)hipGetLastError();      // the refused attribute is not an error of this call
     }
-    // small draft models: one wave per sequence, the weights in LDS, where
-    // the batch fills the chip with one wave per sequence or is tiny (a
-    // workgroup's barriers then cost more than its extra lanes save).
-    // Measured, draft us per round (wave / one workgroup per sequence /
-    // per-step kernels): 4096 sequences 309 / - / 376, 64 sequences 222 /
-    // 147 / 299, 1 sequence 47 / 61 / 128
-    s->wave_draft = D && !D->attnhp() && !(nf && nf[0] == '1') && (B >= 1024 || B <= 8) &&
-                    wave_draft_ok(D->cfg.n_layers, D->d(), D->H(), D->cfg.d_ffn, D->cfg.n_mix, D->cfg.n_types,
-                                  D->bf16());
+    // small draft models: the model in one workgroup's registers while a
+    // sequence per workgroup fills the chip no more than once or twice, then one
+    // wave per sequence with the weights in LDS. Measured, us per 10 drafts after
+    // 40 events (registers / one wave / one workgroup, weights in LDS / per-step
+    // kernels): fp32 d = 32: 4 sequences 55 / 105 / - / 216, 64 sequences 56 / - /
+    // 118 / -, 512 sequences 66 / - / 236 / 306, 1024 sequences 123 / 112 / - / 361;
+    // bf16 d = 64, two layers: 64 sequences 99 / - / 215 / -, 1024 sequences 389
+    // / - / 853 / 605, 2048 sequences 780 / - / - / 747; AttNHP d = 64, two layers:
+    // 64 sequences 85 against 250 of the per-step kernels, 1024 sequences 331
+    // against 416, 2048 sequences 658 against 537. A sequence's whole draft cache
+    // streams through its CU each step, so very long contexts stay with the
+    // kernels that split the keys (8192 events of width 64, two layers: 4 MB a
+    // step, some 40 us, what the per-step kernels take)
+    const bool wave_ok = D && !D->attnhp() &&
+                         wave_draft_ok(D->cfg.n_layers, D->d(), D->H(), D->cfg.d_ffn, D->cfg.n_mix, D->cfg.n_types,
+                                       D->bf16());
+    s->regs_draft = D && !(nf && nf[0] == '1') && max_events <= 8192 &&
+                    B <= (wave_ok ? 512 : D->d() >= 64 ? 1024 : 2048) &&
+                    regs_draft_ok(D->attnhp(), D->bf16(), D->cfg.n_layers, D->d(), D->H(), D->cfg.d_ffn,
+                                  D->cfg.n_mix, D->cfg.n_types);
+    if (s->regs_draft) s->fused_draft = s->fused_w_lds = false;
+    // one wave per sequence: where the batch fills the chip, or is tiny and the
+    // contexts too long for the above (a workgroup's barriers then cost more
+    // than its extra lanes save)
+    s->wave_draft = !s->regs_draft && wave_ok && !(nf && nf[0] == '1') && (B > 512 || B <= 8);
     if (s->wave_draft && allow_draft_wave_lds(LDS_PER_WG - 4096)) {
       s->wave_draft = false;
       (void)hipGetLastError();
     }
     // otherwise, for batches too small to fill the chip with per-step GEMM
     // tiles, the per-step split attention and the row workgroups per sequence
-    s->row_draft = D && !D->attnhp() && !s->fused_draft && !s->wave_draft && !(nf && nf[0] == '1') &&
+    s->row_draft = D && !D->attnhp() && !s->regs_draft && !s->fused_draft && !s->wave_draft && !(nf && nf[0] == '1') &&
                    B <= 256 && s->packD && s->packDdec &&
                    row_draft_ok(D->bf16(), D->cfg.n_layers, D->d(), D->H(), D->cfg.d_ffn, D->cfg.n_mix,
                                 D->cfg.n_types, s->kv_cap);

@@ -139,4 +139,48 @@ __device__ __forceinline__ float wave_max(float v) {
                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 48))));
 }
 
+// rounding to the activation type
+template <typename ELT> __device__ __forceinline__ float rnd_act(float v);
+template <> __device__ __forceinline__ float rnd_act<float>(float v) { return v; }
+template <> __device__ __forceinline__ float rnd_act<bf16_t>(float v) { return bf2f(f2bf(v)); }
+
+// One k step of an MFMA tile product with fp32 accumulation: for every 16x16
+// tile lane l holds row (l mod 16) of A and of W (W is stored [N, K], so its
+// rows are B's columns) over one slice of the k range; the accumulator holds
+// rows 4 (l / 16) + i, column l mod 16.
+//   bf16: v_mfma_f32_16x16x32_bf16, lane slice = 8 consecutive k, 32 k per step.
+//   fp32: v_mfma_f32_16x16x4f32, lane l loads 4 consecutive k (4 (l / 16) .. + 3)
+//         and issues one MFMA per element; across the four MFMAs the 16 k of the
+//         step are each used once, the same k for A and B (K must be a
+//         multiple of 16).
+
+template <typename ELT> struct MfmaStep;
+template <> struct MfmaStep<bf16_t> {
+  static constexpr int KSTEP = 32;
+  typedef bf16x8_t frag;
+  static __device__ __forceinline__ frag load(const bf16_t *p, int g) { return *(const bf16x8_t *)(p + 8 * g); }
+  static __device__ __forceinline__ f32x4_t mma(frag a, frag b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+template <> struct MfmaStep<float> {
+  static constexpr int KSTEP = 16;
+  typedef f32x4_t frag;
+  static __device__ __forceinline__ frag load(const float *p, int g) { return *(const f32x4_t *)(p + 4 * g); }
+  static __device__ __forceinline__ f32x4_t mma(frag a, frag b, f32x4_t c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
+  }
+};
+
+// Workgroup barrier that orders LDS only: global loads into registers and global
+// stores stay in flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 }  // namespace tppsd

@@ -148,6 +148,12 @@ bool wave_draft_ok(int L, int d, int H, int F, int M, int K, int bf16);
 size_t wave_draft_lds_bytes(int L, int D, int F, int M, int K, int elt);
 void launch_draft_wave(const DraftArgs &a, int bf16, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
+// One workgroup per sequence with the whole draft model in its registers
+// (k_draft_regs, tppsd_draft_regs.hip): d_head 16, one or two layers, widths 32
+// and 64 (bf16) or 16 and 32 (fp32), F = 2 d or 4 d, or AttNHP
+bool regs_draft_ok(int attnhp, int bf16, int L, int d, int H, int F, int M, int K);
+void launch_draft_regs(const DraftArgs &a, int attnhp, int bf16, hipStream_t st, hipEvent_t ev0 = nullptr,
+                       hipEvent_t ev1 = nullptr);
 // raises the dynamic LDS limit of the wave-draft kernels; nonzero on failure
 int allow_draft_wave_lds(size_t bytes);
 // elements of the draft's weight matrices (per layer QKV, out, FFN; decoder), each

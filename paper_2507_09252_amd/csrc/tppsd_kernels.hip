@@ -477,37 +477,6 @@ __device__ __forceinline__ void epilogue1(const Epi &e, int r, int n, float acc,
   }
 }
 
-// One k step of an MFMA tile product with fp32 accumulation: for every 16x16
-// tile lane l holds row (l mod 16) of A and of W (W is stored [N, K], so its
-// rows are B's columns) over one slice of the k range; the accumulator holds
-// rows 4 (l / 16) + i, column l mod 16.
-//   bf16: v_mfma_f32_16x16x32_bf16, lane slice = 8 consecutive k, 32 k per step.
-//   fp32: v_mfma_f32_16x16x4f32, lane l loads 4 consecutive k (4 (l / 16) .. + 3)
-//         and issues one MFMA per element; across the four MFMAs the 16 k of the
-//         step are each used once, the same k for A and B (K must be a
-//         multiple of 16).
-
-template <typename ELT> struct MfmaStep;
-template <> struct MfmaStep<bf16_t> {
-  static constexpr int KSTEP = 32;
-  typedef bf16x8_t frag;
-  static __device__ __forceinline__ frag load(const bf16_t *p, int g) { return *(const bf16x8_t *)(p + 8 * g); }
-  static __device__ __forceinline__ f32x4_t mma(frag a, frag b, f32x4_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct MfmaStep<float> {
-  static constexpr int KSTEP = 16;
-  typedef f32x4_t frag;
-  static __device__ __forceinline__ frag load(const float *p, int g) { return *(const f32x4_t *)(p + 4 * g); }
-  static __device__ __forceinline__ f32x4_t mma(frag a, frag b, f32x4_t c) {
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
-  }
-};
-
 // LDS-staged GEMM with fp32 accumulation: a workgroup of 4 waves (2 x 2)
 // owns a BM x BN output tile and walks K in stages of BK = KSN MFMA k-steps
 // (each stage costs a barrier and an LDS round trip, so tiles with few rows
@@ -752,14 +721,6 @@ __global__ __launch_bounds__(256) void k_gemm_lds(const ELT *__restrict__ X, con
 // holding D / 16 consecutive values each. The barriers order LDS only, so
 // weight loads stay in flight across them.
 // ---------------------------------------------------------------------------
-// Workgroup barrier that orders LDS only: global loads into registers and global
-// stores stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // W [N][K] (bf16, N a multiple of 16, K of 32) into MFMA operand fragments:
 // fragment (nt, ks) holds, for lane l = 16 g + r, W[16 nt + r][32 ks + 8 g ..
 // + 7] at ((nt K/32 + ks) 64 + l) 8, so that a wave reads one fragment as 1 KB
@@ -1638,10 +1599,6 @@ __global__ __launch_bounds__(256) void k_head(const float *__restrict__ logits, 
 // LDS; keys/values go to the draft KV cache exactly as in the layered path,
 // with the same bf16 rounding points.
 // ---------------------------------------------------------------------------
-
-template <typename ELT> __device__ __forceinline__ float rnd_act(float v);
-template <> __device__ __forceinline__ float rnd_act<float>(float v) { return v; }
-template <> __device__ __forceinline__ float rnd_act<bf16_t>(float v) { return bf2f(f2bf(v)); }
 
 template <typename ELT> __device__ __forceinline__ void load8(const ELT *p, float w[8]);
 template <> __device__ __forceinline__ void load8<float>(const float *p, float w[8]) {
