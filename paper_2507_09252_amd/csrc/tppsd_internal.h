@@ -343,6 +343,8 @@ void launch_prefill_init(const float *ht, const int32_t *hk, int B, int n0, int 
                          float *ev_t, int32_t *ev_k, int ev_stride, int32_t *n, int32_t *gen, int32_t *lenT,
                          int32_t *lenD, int32_t *done, int32_t *rnd, int32_t *zeros, float *t_end, double *ll,
                          int32_t *n_done, uint32_t *status, unsigned long long *acc_stats, hipStream_t st);
+// *left = the most events an unfinished sequence still has to generate (0: all finished)
+void launch_left(const int32_t *gen, const int32_t *done, int n_gen, int B, int32_t *left, hipStream_t st);
 void launch_snapshot(const int32_t *src, int32_t *dst, int B, hipStream_t st);
 void launch_copy_events(const float *ev_t, const int32_t *ev_k, const int32_t *n, int B, int ev_stride,
                         float *t, int32_t *k, int32_t *nout, hipStream_t st);

@@ -3861,6 +3861,21 @@ __global__ __launch_bounds__(256) void k_count_done(const int32_t *done, int B, 
   if (threadIdx.x == 0) *n_done = part[0];
 }
 
+// the most events a sequence still has to generate (one workgroup)
+__global__ __launch_bounds__(256) void k_left(const int32_t *gen, const int32_t *done, int n_gen, int B,
+                                              int32_t *left) {
+  __shared__ int part[256];
+  int m = 0;
+  for (int i = threadIdx.x; i < B; i += 256) m = max(m, done[i] ? 0 : n_gen - gen[i]);
+  part[threadIdx.x] = m;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) part[threadIdx.x] = max(part[threadIdx.x], part[threadIdx.x + h]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *left = part[0];
+}
+
 __global__ void k_snapshot(const int32_t *src, int32_t *dst, int B) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < B) dst[i] = src[i];
@@ -4075,6 +4090,10 @@ void launch_prefill_init(const float *ht, const int32_t *hk, int B, int n0, int 
   k_prefill_init<<<(total + 255) / 256, 256, 0, s>>>(ht, hk, B, n0, n_gen, t_end_in, ev_t, ev_k, ev_stride, n, gen,
                                                      lenT, lenD, done, rnd, zeros, t_end, ll, status, acc_stats);
   k_count_done<<<1, 256, 0, s>>>(done, B, n_done);
+}
+
+void launch_left(const int32_t *gen, const int32_t *done, int n_gen, int B, int32_t *left, hipStream_t s) {
+  k_left<<<1, 256, 0, s>>>(gen, done, n_gen, B, left);
 }
 
 void launch_snapshot(const int32_t *src, int32_t *dst, int B, hipStream_t s) {
