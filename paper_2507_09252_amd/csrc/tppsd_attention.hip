@@ -172,19 +172,18 @@ __global__ __launch_bounds__(64 * NW) void k_attn_mfma(int H, int P, const int32
         const int key = kt + 8 * g + j;
         const float raw = (j < 4) ? s0[j] : s1[j - 4];
         const bool ok = interior || (q_ok && key < k_end && key <= my_last);
-        sv[j] = ok ? raw * scale2 : -INFINITY;
+        sv[j] = ok ? raw : -INFINITY;
         mx = fmaxf(mx, sv[j]);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run[t], mx);
+      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)) * scale2);
       // (exp2 of -inf is 0: masked keys and an empty running state drop out)
       const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
       const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
       uint32_t pw[4];
 #pragma unroll
       for (int j = 0; j < 8; j += 2)
-        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
+        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(fmaf(sv[j], scale2, -m_ref)),
+                           __builtin_amdgcn_exp2f(fmaf(sv[j + 1], scale2, -m_ref)));
       // P V takes the probabilities in bf16; the normaliser (the ones rows)
       // sums the same rounded values, so the output stays a convex
       // combination of values
@@ -487,7 +486,7 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
                                                    int sink) {
   constexpr int KT = 32, NDT = DH / 16, NC = DH >= 32 ? DH / 32 : 1;
   const int bh = blockIdx.x, b = bh / H, h = bh - b * H;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
   const int d = H * DH;
   const int q0 = ((gridDim.y - 1 - blockIdx.y) * 4 + wave) * 16 * QT;
   if (q0 >= P) return;
@@ -528,21 +527,22 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
   // (unconditional: rows past the slab and value blocks past the key range
   // are clamped into them and masked below)
   auto fetch = [&](Step &f, int kt) {
-    const size_t r0 = kvbase + min(kt + krow0, cap - 1), r1 = kvbase + min(kt + krow1, cap - 1);
+    const bf16_t *kp = kc + (kvbase + kt) * DH, *vp = vc + (kvbase + kt) * DH;   // (uniform)
+    const int left = cap - 1 - kt;
+    const int r0 = min(krow0, left) * DH, r1 = min(krow1, left) * DH;
     if (DH >= 32) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        f.a0[c] = *(const bf16x8_t *)(kc + r0 * DH + 32 * c + 8 * g);
-        f.a1[c] = *(const bf16x8_t *)(kc + r1 * DH + 32 * c + 8 * g);
+        f.a0[c] = *(const bf16x8_t *)(kp + (r0 + 32 * c + 8 * g));
+        f.a1[c] = *(const bf16x8_t *)(kp + (r1 + 32 * c + 8 * g));
       }
     } else {
-      f.b0 = *(const short4_t *)(kc + r0 * DH + 4 * g);
-      f.b1 = *(const short4_t *)(kc + r1 * DH + 4 * g);
+      f.b0 = *(const short4_t *)(kp + (r0 + 4 * g));
+      f.b1 = *(const short4_t *)(kp + (r1 + 4 * g));
     }
-    const int k8c = min(kt + 8 * g, (k_end - 1) & ~7);
+    const int v0 = min(g, ((k_end - 1) >> 3) - (kt >> 3)) * (8 * DH) + rr * 8;
 #pragma unroll
-    for (int td = 0; td < NDT; ++td)
-      f.vw[td] = *(const uint4 *)(vc + kvbase * DH + (size_t)(k8c >> 3) * (8 * DH) + (16 * td + rr) * 8);
+    for (int td = 0; td < NDT; ++td) f.vw[td] = *(const uint4 *)(vp + (v0 + 128 * td));
   };
   Step cur, nxt;
   if (k_end > 0) fetch(cur, 0);
@@ -585,18 +585,17 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
         const int key = kt + 8 * g + j;
         const float raw = (j < 4) ? s0[j] : s1[j - 4];
         const bool ok = interior || (key < k_end && key <= my_last);
-        sv[j] = ok ? raw * scale2 : -INFINITY;
+        sv[j] = ok ? raw : -INFINITY;
         mx = fmaxf(mx, sv[j]);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m_run[t], mx);
+      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)) * scale2);
       const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
       const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
       uint32_t pw[4];
 #pragma unroll
       for (int j = 0; j < 8; j += 2)
-        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
+        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(fmaf(sv[j], scale2, -m_ref)),
+                           __builtin_amdgcn_exp2f(fmaf(sv[j + 1], scale2, -m_ref)));
       const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, (uint4){pw[0], pw[1], pw[2], pw[3]});
       m_run[t] = m_new;
       if (__ballot(alpha != 1.f) != 0ull) {
@@ -641,7 +640,7 @@ __global__ __launch_bounds__(256) void k_attn_rows_f32(int H, int P, const int32
                                                        int sink) {
   constexpr int KT = 32, NDT = DH / 16;
   const int bh = blockIdx.x, b = bh / H, h = bh - b * H;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
   const int d = H * DH;
   const int q0 = ((gridDim.y - 1 - blockIdx.y) * 4 + wave) * 16 * QT;
   if (q0 >= P) return;

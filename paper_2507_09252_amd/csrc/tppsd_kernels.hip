@@ -1406,23 +1406,35 @@ __global__ __launch_bounds__(256) void k_gemm_tall(const bf16_t *__restrict__ X,
     // a tile of values: lanes over 8 rows x 8 columns, whose elements of the
     // position-blocked cache are 128 contiguous bytes (row by row they would
     // be single elements 16 bytes apart)
-    for (int i = tid; i < BM * BN; i += 256) {
-      const int col = (i >> 3) % BN, row = (i & 7) + 8 * ((i >> 3) / BN);
-      const int r = m0 + row, c = n0 + col - 2 * e.d;
-      if (r >= T) continue;
+    // (this thread: rows tid % 8 + 8 i, columns tid / 8 + 32 k)
+    float bias[BN / 32];
+    size_t off[BN / 32];   // of the column in a sequence's caches, position 0
+#pragma unroll
+    for (int k = 0; k < BN / 32; ++k) {
+      const int col = (tid >> 3) + 32 * k, c = n0 + col - 2 * e.d, h = c / e.dh;
+      bias[k] = e.bias[n0 + col];
+      off[k] = (size_t)h * e.cap * e.dh + (c - h * e.dh) * 8;
+    }
+#pragma unroll 4
+    for (int i = 0; i < BM / 8; ++i) {
+      const int row = (tid & 7) + 8 * i, r = m0 + row;
+      if (r >= T) break;
       const int b = r / e.P, pos = e.start[b] + e.start_off + (r - b * e.P);
-      if (pos < e.cap)
-        st((bf16_t *)e.vc, v_at<bf16_t>(((size_t)b * e.H + c / e.dh) * e.cap, pos, c % e.dh, e.dh),
-           Cs[row * CLD + col] + e.bias[n0 + col]);
-      else
+      if (pos >= e.cap) {
         atomicOr(e.status, TPPSD_STATUS_CAPACITY);
+        continue;
+      }
+      bf16_t *vp = (bf16_t *)e.vc + (size_t)b * e.H * e.cap * e.dh + (size_t)(pos >> 3) * (8 * e.dh) + (pos & 7);
+#pragma unroll
+      for (int k = 0; k < BN / 32; ++k) vp[off[k]] = f2bf(Cs[row * CLD + (tid >> 3) + 32 * k] + bias[k]);
     }
     return;
   }
-  for (int i = tid; i < BM * (BN / 8); i += 256) {
-    const int row = i / (BN / 8), c8 = i % (BN / 8);
-    const int r = m0 + row, n = n0 + 8 * c8;
-    if (r >= T) continue;
+  const int c8 = tid % (BN / 8), n = n0 + 8 * c8;   // (a thread's columns are the same in every row)
+#pragma unroll 2
+  for (int row = tid / (BN / 8); row < BM; row += 256 / (BN / 8)) {
+    const int r = m0 + row;
+    if (r >= T) break;
     float cv[8];
     Epi8In in;
     epilogue8_fetch(e, r, n, in);
