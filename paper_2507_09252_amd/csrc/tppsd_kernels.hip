@@ -1202,39 +1202,66 @@ __global__ __launch_bounds__(256) void k_gemm_dl(const bf16_t *__restrict__ X, c
 // KB; a tile walked stage by stage through LDS pays a barrier and an LDS
 // round trip per stage, and 32 x 32 tiles leave most CUs idle (N = 512: 16
 // workgroups). The order of the waves' sums is fixed. Measured at 32 rows
-// against the tile walked in stages: N = 512, K = 512 4.1 us and K = 2048 6.3
-// (6.8 on average); with a LayerNorm operand, K = 512, N = 1536 5.6 vs 8.0 and
-// N = 2048 5.1 vs 7.8; the decoder heads (53 columns, K = 2048) 5.8 vs 9.6.
+// against the tile walked in stages: N = 512, K = 512 4.4 us and K = 2048 3.7
+// (6.8 on average); with a LayerNorm operand, K = 512, N = 1536 4.6 vs 8.0 and
+// N = 2048 4.2 vs 7.8; the decoder heads (53 columns, K = 2048) 3.1 vs 9.6.
 // LN: the A operand is LayerNorm(x) of the fp32 stream x, normalised in the
 // operand registers; each wave's share of a row's sum, then of its squared
 // deviations (two passes over the registers), goes through LDS.
 // ---------------------------------------------------------------------------
+// One wave's share of a 16-row operand, NCH 16-byte chunks per row, moved
+// straight into LDS and read back as fragments. A fragment read from a
+// row-major matrix by its own lanes has adjacent lanes 16 rows apart, one
+// cache access each (some 64 cycles an instruction); here adjacent lanes take
+// consecutive chunks of a row. Blocks of CPR chunks per row; chunk c of row r
+// is stored at chunk c ^ ((r CPR / 16) mod CPR), which spreads a fragment
+// read's 16 rows over all banks.
+template <int NCH> struct RowsTile {
+  static constexpr int CPR = NCH < 8 ? NCH : 8, NBLK = NCH / CPR, IPB = CPR / 4;   // instructions per block
+  static constexpr int BYTES = 16 * NCH * 16;
+  static_assert(NCH % CPR == 0 && CPR >= 4, "chunks per row");
+  static __device__ __forceinline__ int swz(int row) { return (row * CPR / 16) & (CPR - 1); }
+  // src(row): the wave's first chunk of a row (clamped by the caller); lds: the wave's region
+  template <typename F> static __device__ __forceinline__ void load(char *lds, int lane, F src) {
+#pragma unroll
+    for (int i = 0; i < IPB; ++i) {
+      const int p = 64 * i + lane, row = p / CPR;
+      const char *sp = src(row) + ((p % CPR) ^ swz(row)) * 16;
+#pragma unroll
+      for (int b = 0; b < NBLK; ++b)
+        __builtin_amdgcn_global_load_lds((const void *)(sp + b * CPR * 16), (lds_ptr_t)(lds + (b * IPB + i) * 1024), 16,
+                                         0, 0);
+    }
+  }
+  static __device__ __forceinline__ uint4 chunk(const char *lds, int row, int q) {
+    return *(const uint4 *)(lds + ((q / CPR) * 16 * CPR + row * CPR + ((q % CPR) ^ swz(row))) * 16);
+  }
+};
+
 template <typename ELT, int NW, int NS, bool LN>
 __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X, const float *__restrict__ xf,
                                                        const float *__restrict__ lg, const float *__restrict__ lb,
                                                        const ELT *__restrict__ W, int T, int N, int K, Epi e) {
   typedef MfmaStep<ELT> S;
   constexpr int KS = S::KSTEP, VE = 16 / sizeof(ELT), LD = 20;
-  __shared__ __attribute__((aligned(16))) float red[NW][16 * LD];
+  constexpr int XE = LN ? 4 : sizeof(ELT);               // bytes of an operand element as read
+  typedef RowsTile<NS * KS * XE / 16> TA;
+  typedef RowsTile<NS * KS * (int)sizeof(ELT) / 16> TB;
+  __shared__ __attribute__((aligned(1024))) char ops[NW * (TA::BYTES + TB::BYTES)];
+  __shared__ __attribute__((aligned(16))) float red[NW * 16 * LD];
   __shared__ __attribute__((aligned(16))) float st1[LN ? 16 * NW : 4], st2[LN ? 16 * NW : 4];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rr = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rr = lane & 15, g = lane >> 4;
   const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
-  const int k0 = wave * NS * KS + VE * g;
+  const int kw = wave * NS * KS;                         // the wave's first k
+  char *const la = ops + wave * (TA::BYTES + TB::BYTES), *const lw = la + TA::BYTES;
   // (rows past T and columns past N are clamped; their results are not stored)
-  const size_t xoff = (size_t)min(m0 + rr, T - 1) * K + k0, woff = (size_t)min(n0 + rr, N - 1) * K + k0;
-  uint4 a[NS], b[NS];
-  float4 xv[LN ? NS : 1][VE / 4], gv[LN ? NS : 1][VE / 4], bv[LN ? NS : 1][VE / 4];
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    if (LN) {
-#pragma unroll
-      for (int c = 0; c < VE / 4; ++c) xv[s][c] = *(const float4 *)(xf + xoff + s * KS + 4 * c);
-    } else {
-      a[s] = *(const uint4 *)(X + xoff + s * KS);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < NS; ++s) b[s] = *(const uint4 *)(W + woff + s * KS);
+  const char *xbase = LN ? (const char *)xf : (const char *)X;
+  auto xrow = [&](int row) { return xbase + ((size_t)min(m0 + row, T - 1) * K + kw) * XE; };
+  auto wrow = [&](int row) { return (const char *)(W + (size_t)min(n0 + row, N - 1) * K + kw); };
+  TA::load(la, lane, xrow);
+  TB::load(lw, lane, wrow);
+  const int k0 = kw + VE * g;
+  float4 gv[LN ? NS : 1][VE / 4], bv[LN ? NS : 1][VE / 4];
   if (LN) {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
@@ -1249,6 +1276,20 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X
   float ebias = 0.f, eres = 0.f;
   int epos = 0;
   epilogue_fetch(e, min(r, T - 1), min(n, N - 1), ebias, eres, epos);
+  wait_vmcnt<0>();   // this wave's operands are in LDS (nobody else reads them)
+  uint4 a[NS], b[NS];
+  float4 xv[LN ? NS : 1][VE / 4];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    if (LN) {
+#pragma unroll
+      for (int c = 0; c < VE / 4; ++c)
+        xv[s][c] = __builtin_bit_cast(float4, TA::chunk(la, rr, (s * KS + VE * g) / 4 + c));
+    } else {
+      a[s] = TA::chunk(la, rr, 4 * s + g);
+    }
+    b[s] = TB::chunk(lw, rr, 4 * s + g);
+  }
   if (LN) {
     float s1 = 0.f;
 #pragma unroll
@@ -1300,12 +1341,12 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X
   for (int s = 0; s < NS; ++s)
     acc = S::mma(__builtin_bit_cast(typename S::frag, a[s]), __builtin_bit_cast(typename S::frag, b[s]), acc);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) red[wave][(4 * g + v) * LD + rr] = acc[v];
+  for (int v = 0; v < 4; ++v) red[(wave * 16 + 4 * g + v) * LD + rr] = acc[v];
   lds_barrier();
   if (tid >= 256 || r >= T || n >= N) return;
   float y = 0.f;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) y += red[w][(tid >> 4) * LD + (tid & 15)];
+  for (int w = 0; w < NW; ++w) y += red[(w * 16 + (tid >> 4)) * LD + (tid & 15)];
   epilogue1<ELT>(e, r, n, y, ebias, eres, epos);
 }
 
@@ -3964,11 +4005,11 @@ static void gemm_dispatch(const void *X, const LnA *ln, const void *W, int T, in
   // few rows, K a power of two of the k-steps that have an instance: 16 x 16
   // tiles with K split over the waves. What a CU takes in bounds it (48 KB a
   // tile at K = 512), so the rule is on the rows. Measured, one AR step, this
-  // kernel against the 32 x 32 tiles below: d = 512 (8 layers) 32 rows 223 vs
-  // 321 us, 128 rows 413 vs 438, 256 rows 696 vs 609; d = 256 (6 layers) 32
-  // rows 128 vs 167, 256 rows 261 vs 273, 272 rows (verify) 186 vs 170; fp32
-  // d = 64 (4 layers) 256 rows 121 vs 142. (32 x 32 tiles with K split the
-  // same way take in as much per CU over fewer CUs: 32 rows 306 us.)
+  // kernel against the 32 x 32 tiles below: d = 512 (8 layers) 32 rows 195 vs
+  // 321 us, 128 rows 369 vs 438, 256 rows (operands by the lanes' own loads)
+  // 696 vs 609; d = 256 (6 layers) 32 rows 115 vs 167, 128 rows 166 vs 209; fp32
+  // d = 64 (4 layers) 256 rows 120 vs 142. (32 x 32 tiles with K split the same
+  // way take in as much per CU over fewer CUs: 32 rows 306 us.)
   const int ksteps = K % MfmaStep<ELT>::KSTEP ? 0 : K / MfmaStep<ELT>::KSTEP;
   if ((T <= 128 || (T <= 256 && K <= 256)) &&
       (ksteps == 4 || ksteps == 8 || ksteps == 16 || (!ln && (ksteps == 32 || ksteps == 64)))) {
