@@ -854,6 +854,60 @@ int do_draft_poisson(tppsd_state *s, int gamma, const float *params, const tppsd
   return hip_check("tppsd_draft_poisson");
 }
 
+// small targets: a whole pass over P positions per sequence (the verify pass, or
+// an AR step, P = 1) with one workgroup per sequence; dr_t / dr_k: the positions
+// after the pending event
+bool seq_pass_ok(const tppsd_state *s, int P) {
+  const tppsd_model *m = s->T;
+  return !m->attnhp() && verify_seq_ok(m->bf16(), m->cfg.n_layers, m->d(), m->H(), m->cfg.d_ffn, P, s->kv_cap);
+}
+
+void seq_pass(tppsd_state *s, int P, const HeadArgs &h, const float *dr_t, const int32_t *dr_k, int dr_stride,
+              hipStream_t st) {
+  const tppsd_model *m = s->T;
+  VerifySeqArgs a{};
+  a.P = P;
+  a.d = m->d();
+  a.F = m->cfg.d_ffn;
+  a.H = m->H();
+  a.L = m->cfg.n_layers;
+  a.M = m->cfg.n_mix;
+  a.K = m->cfg.n_types;
+  for (int l = 0; l < a.L; ++l) {
+    const LayerW &w = m->layers[l];
+    // (k_verify_seq reads its matrices in the packed order)
+    a.layer[l] = {s->cT.wb_qkv[l], s->cT.wb_out[l], s->cT.wb_f1[l], s->cT.wb_f2[l], w.ln1_g, w.ln1_b, w.qkv_b,
+                  w.out_b, w.ln2_g, w.ln2_b, w.ffn1_b, w.ffn2_b};
+  }
+  a.type_emb = m->type_emb;
+  a.Ek1_w = s->cT.wb_ek1;
+  a.mix_w = m->mix_w;
+  a.k2_w = m->k2_w;
+  a.lnf_g = m->lnf_g;
+  a.lnf_b = m->lnf_b;
+  a.k1_b = m->k1_b;
+  a.head_b = s->cT.head_b;
+  a.freq = s->cT.freq;
+  a.kc = s->cT.k;
+  a.vc = s->cT.v;
+  a.layer_bytes = s->cT.layer_bytes;
+  a.cap = s->kv_cap;
+  a.ev_t = s->ev_t;
+  a.ev_k = s->ev_k;
+  a.ev_stride = s->cap;
+  a.lenT = s->lenT;
+  a.done = s->done;
+  a.dr_t = dr_t;
+  a.dr_k = dr_k;
+  a.dr_stride = dr_stride;
+  a.status = s->status;
+  a.h = h;
+  const bool timed = s->cur_ev != nullptr;
+  if (timed) s->ev_used[m->cfg.n_layers] = 1;
+  launch_verify_seq(a, s->B, m->bf16(), st, timed ? s->cur_ev[2 * m->cfg.n_layers] : nullptr,
+                    timed ? s->cur_ev[2 * m->cfg.n_layers + 1] : nullptr);
+}
+
 int do_verify(tppsd_state *s, int gamma, const tppsd_draft_buf *in, const tppsd_verify_buf *out, hipStream_t st) {
   TokSrc src{};
   src.ev_t = s->ev_t;
@@ -880,51 +934,8 @@ int do_verify(tppsd_state *s, int gamma, const tppsd_draft_buf *in, const tppsd_
   h.dr_stride = s->max_gamma;
   h.v_logg = out->logg;
   h.v_logf = out->logf;
-  const tppsd_model *m = s->T;
-  if (!m->attnhp() &&
-      verify_seq_ok(m->bf16(), m->cfg.n_layers, m->d(), m->H(), m->cfg.d_ffn, m->cfg.n_mix, m->cfg.n_types,
-                    gamma + 1)) {
-    // small targets: the whole pass of a sequence in one workgroup
-    VerifySeqArgs a{};
-    a.P = gamma + 1;
-    a.d = m->d();
-    a.F = m->cfg.d_ffn;
-    a.H = m->H();
-    a.L = m->cfg.n_layers;
-    a.M = m->cfg.n_mix;
-    a.K = m->cfg.n_types;
-    for (int l = 0; l < a.L; ++l) {
-      const LayerW &w = m->layers[l];
-      // (k_verify_seq reads its matrices in the packed order)
-      a.layer[l] = {s->cT.wb_qkv[l], s->cT.wb_out[l], s->cT.wb_f1[l], s->cT.wb_f2[l], w.ln1_g, w.ln1_b, w.qkv_b,
-                    w.out_b, w.ln2_g, w.ln2_b, w.ffn1_b, w.ffn2_b};
-    }
-    a.type_emb = m->type_emb;
-    a.Ek1_w = s->cT.wb_ek1;
-    a.head_w = s->cT.wb_head;
-    a.lnf_g = m->lnf_g;
-    a.lnf_b = m->lnf_b;
-    a.k1_b = m->k1_b;
-    a.head_b = s->cT.head_b;
-    a.freq = s->cT.freq;
-    a.kc = s->cT.k;
-    a.vc = s->cT.v;
-    a.layer_bytes = s->cT.layer_bytes;
-    a.cap = s->kv_cap;
-    a.ev_t = s->ev_t;
-    a.ev_k = s->ev_k;
-    a.ev_stride = s->cap;
-    a.lenT = s->lenT;
-    a.done = s->done;
-    a.dr_t = in->t;
-    a.dr_k = in->k;
-    a.dr_stride = s->max_gamma;
-    a.status = s->status;
-    a.h = h;
-    const bool timed = s->cur_ev != nullptr;
-    if (timed) s->ev_used[m->cfg.n_layers] = 1;
-    launch_verify_seq(a, s->B, m->bf16(), st, timed ? s->cur_ev[2 * m->cfg.n_layers] : nullptr,
-                      timed ? s->cur_ev[2 * m->cfg.n_layers + 1] : nullptr);
+  if (seq_pass_ok(s, gamma + 1)) {
+    seq_pass(s, gamma + 1, h, in->t, in->k, s->max_gamma, st);
     return hip_check("tppsd_verify");
   }
   int rc = forward(s, s->T, s->cT, s->lenT, 0, gamma + 1, src, &h, true, st);
@@ -1551,6 +1562,11 @@ int ar_step(tppsd_state *s, int out_stride, float *d_t_out, int32_t *d_k_out, hi
   h.ar_k_out = d_k_out;
   h.ar_out_stride = out_stride;
   h.gen0 = s->gen0;
+  if (seq_pass_ok(s, 1)) {
+    // (no positions after the pending event: the kernel's unconditional read of them gets an event)
+    seq_pass(s, 1, h, s->ev_t, s->ev_k, 0, st);
+    return hip_check("tppsd_sample_ar");
+  }
   return forward(s, s->T, s->cT, s->lenT, 0, 1, src, &h, false, st);
 }
 

@@ -183,4 +183,46 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// sums and maxima over a wave, or over aligned groups of W lanes, left in every
+// lane: DPP within rows of 16, then row and half-wave swaps
+template <int W> __device__ __forceinline__ float lanes_sum(float v) {
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x124>(v);   // row_ror:4
+  v += dpp_mov<0x128>(v);   // row_ror:8
+  if (W >= 32) v = xor16_sum(v);
+  if (W >= 64) v = xor32_sum(v);
+  return v;
+}
+__device__ __forceinline__ float lanes_max(float v) {
+  v = fmaxf(v, dpp_mov<0xB1>(v));
+  v = fmaxf(v, dpp_mov<0x4E>(v));
+  v = fmaxf(v, dpp_mov<0x124>(v));
+  v = fmaxf(v, dpp_mov<0x128>(v));
+  return xor32_max(xor16_max(v));
+}
+// 1 / sqrt(v) and 1 / v for normal v: the hardware's approximation (1 ulp)
+// and one Newton step
+__device__ __forceinline__ float rsqrt_nr(float v) {
+  const float y = __builtin_amdgcn_rsqf(v);
+  return y * fmaf(-0.5f * v * y, y, 1.5f);
+}
+__device__ __forceinline__ float rcp_nr(float v) {
+  const float y = __builtin_amdgcn_rcpf(v);
+  return y * fmaf(-v, y, 2.f);
+}
+
+// exponentials of the attention: bf16 scores are kept in base-2 units
+template <typename ELT> __device__ __forceinline__ float exp_score(float x);
+template <> __device__ __forceinline__ float exp_score<bf16_t>(float x) { return __builtin_amdgcn_exp2f(x); }
+template <> __device__ __forceinline__ float exp_score<float>(float x) { return expf(x); }
+
+// LDS traffic of one wave stays in order: only the compiler has to keep a
+// write ahead of the other lanes' reads of it
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace tppsd

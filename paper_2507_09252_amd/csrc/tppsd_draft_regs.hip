@@ -55,11 +55,6 @@ namespace {
 constexpr int DG_TAIL = 64;   // positions of the round kept in LDS (gamma + 1 <= 33), one step of 64
 constexpr int DG_HEAD_TILES = 8;   // 16-row tiles of the decoder heads
 
-// exponentials of the attention: bf16 scores are kept in base-2 units
-template <typename ELT> __device__ __forceinline__ float dg_exp(float x);
-template <> __device__ __forceinline__ float dg_exp<bf16_t>(float x) { return __builtin_amdgcn_exp2f(x); }
-template <> __device__ __forceinline__ float dg_exp<float>(float x) { return expf(x); }
-
 template <typename ELT> struct DgFrag;
 template <> struct DgFrag<bf16_t> {
   typedef bf16x8_t frag;
@@ -72,35 +67,6 @@ template <> struct DgFrag<float> {
   typedef f32x4_t frag;
   static __device__ __forceinline__ frag pack(const float *v) { return (f32x4_t){v[0], v[1], v[2], v[3]}; }
 };
-
-// sums and maxima over a wave, or over aligned groups of W lanes, left in every
-// lane: DPP within rows of 16, then row and half-wave swaps
-template <int W> __device__ __forceinline__ float dg_sum(float v) {
-  v += dpp_mov<0xB1>(v);
-  v += dpp_mov<0x4E>(v);
-  v += dpp_mov<0x124>(v);   // row_ror:4
-  v += dpp_mov<0x128>(v);   // row_ror:8
-  if (W >= 32) v = xor16_sum(v);
-  if (W >= 64) v = xor32_sum(v);
-  return v;
-}
-__device__ __forceinline__ float dg_max(float v) {
-  v = fmaxf(v, dpp_mov<0xB1>(v));
-  v = fmaxf(v, dpp_mov<0x4E>(v));
-  v = fmaxf(v, dpp_mov<0x124>(v));
-  v = fmaxf(v, dpp_mov<0x128>(v));
-  return xor32_max(xor16_max(v));
-}
-// 1 / sqrt(v) and 1 / v for normal v: the hardware's approximation (1 ulp)
-// and one Newton step
-__device__ __forceinline__ float dg_rsqrt(float v) {
-  const float y = __builtin_amdgcn_rsqf(v);
-  return y * fmaf(-0.5f * v * y, y, 1.5f);
-}
-__device__ __forceinline__ float dg_rcp(float v) {
-  const float y = __builtin_amdgcn_rcpf(v);
-  return y * fmaf(-v, y, 2.f);
-}
 
 // Attention over 64 consecutive cached positions of one head, d_head = 16:
 // keys kt + lane scored one per lane; probabilities come back from LDS.
@@ -325,14 +291,6 @@ template <> struct DgTile<float> {
   static __device__ __forceinline__ void store(float *p, const float (&v)[NE]) { *p = v[0]; }
 };
 
-// LDS traffic of one wave stays in order: only the compiler has to keep a
-// write ahead of the other lanes' reads of it
-__device__ __forceinline__ void dg_wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // D: model width, F: FFN width (0: AttNHP), L: layers, NW: waves
 template <typename ELT, int D, int F, int L, int NW>
 __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
@@ -534,11 +492,11 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         if (i >= P) break;
-        const float mean = dg_sum<D>(x[i]) / (float)D, c = x[i] - mean;
-        const float rstd = dg_rsqrt(dg_sum<D>(c * c) / (float)D + 1e-5f);
+        const float mean = lanes_sum<D>(x[i]) / (float)D, c = x[i] - mean;
+        const float rstd = rsqrt_nr(lanes_sum<D>(c * c) / (float)D + 1e-5f);
         to_operand(i, c * rstd * gn[j] + bt[j]);
       }
-      dg_wave_sync();
+      wave_lds_order();
     };
     auto operand = [&](int t, int s) -> frag { return *(const frag *)&as[wave][t][k_of(s)]; };
     // this lane's element of the attention output of the layer whose partials are in pm
@@ -550,15 +508,15 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
         m[w] = pm[hh * WPH + w][t][0];
         Mx = fmaxf(Mx, m[w]);
       }
-      float Ls = NHP ? dg_exp<ELT>(-Mx) : 0.f, o = 0.f;
+      float Ls = NHP ? exp_score<ELT>(-Mx) : 0.f, o = 0.f;
 #pragma unroll
       for (int w = 0; w < WPH; ++w) {
         const float *r = pm[hh * WPH + w][t];
-        const float f = (m[w] == -INFINITY) ? 0.f : dg_exp<ELT>(m[w] - Mx);
+        const float f = (m[w] == -INFINITY) ? 0.f : exp_score<ELT>(m[w] - Mx);
         Ls += r[1] * f;
         o += r[4 + j % DH] * f;
       }
-      return rnd_act<ELT>(Ls > 0.f ? o * dg_rcp(Ls) : 0.f);
+      return rnd_act<ELT>(Ls > 0.f ? o * rcp_nr(Ls) : 0.f);
     };
 
 #pragma unroll
@@ -580,7 +538,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
           if (ly > 0) x[i] += tanhf(merged(i));
           to_operand(i, x[i]);
         }
-        dg_wave_sync();
+        wave_lds_order();
       } else {
         if (ly > 0) add(pB, KGF, lv - LV + 8 * D);
         norm(lv + 3 * D, lv + 4 * D);
@@ -634,18 +592,18 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
             float mx = sc[p][0];
 #pragma unroll
             for (int i = 1; i < NB; ++i) mx = fmaxf(mx, sc[p][i]);
-            const float m_new = fmaxf(m_run[p], dg_max(mx));
+            const float m_new = fmaxf(m_run[p], lanes_max(mx));
             const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-            al[p] = dg_exp<ELT>(m_run[p] - m_ref);
+            al[p] = exp_score<ELT>(m_run[p] - m_ref);
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
               if (i >= ns) break;   // uniform
-              st(&pbuf[wave][p][0], 64 * i + lane, dg_exp<ELT>(sc[p][i] - m_ref));
+              st(&pbuf[wave][p][0], 64 * i + lane, exp_score<ELT>(sc[p][i] - m_ref));
             }
             m_run[p] = m_new;
           }
           at.rescale(al[0], al[1], lane);
-          dg_wave_sync();
+          wave_lds_order();
         };
         const int nbt = (mine + NB - 1) / NB;
         const int nly = ly + 1 == L ? 0 : ly + 1;    // the next attention's layer
@@ -670,7 +628,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
             if (idx >= mine) break;   // uniform
             at.apply(kv[i], &pbuf[wave][0][64 * i], NB * 64, P, base - 64 * (sub + WPH * idx), lane);
           }
-          dg_wave_sync();
+          wave_lds_order();
           fetch_v(more ? ly : nly, more ? bt + 1 : 0);
         }
         if (sub == nst % WPH) {
@@ -687,7 +645,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
           sc[1][0] = in_cap && lane <= off0 + 1 ? s1 * scale : -INFINITY;
           softmax(sc, 1);
           at.apply(tl, &pbuf[wave][0][0], NB * 64, P, 64, lane);
-          dg_wave_sync();
+          wave_lds_order();
         }
         at.finish(&pm[wave][0][0], DH + 4, P, lane);
         if (lane == 0) {
@@ -705,11 +663,11 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
             if (i >= P) break;
             to_operand(i, merged(i));
           }
-          dg_wave_sync();
+          wave_lds_order();
           float y[NE];
           Tile::template mul<NO>(wo[ly], [&](int t, int s) -> frag { return operand(t, kg * NO + s); }, P, lane, y);
           if (tk < P) Tile::store(&pA[kg][tk][16 * tn + ne0], y);
-          dg_wave_sync();
+          wave_lds_order();
         }
         lds_barrier();
         phase();
@@ -748,7 +706,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
         x[i] += tanhf(merged(i));
         to_operand(i, x[i]);
       }
-      dg_wave_sync();
+      wave_lds_order();
     } else {
       add(pB, KGF, vec + (L - 1) * LV + 8 * D);
       norm(hvec, hvec + D);
@@ -796,7 +754,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
     // lane's logit -> the log of the softmax's denominator (in lse) and the
     // first index whose running sum exceeds u times the total
     auto draw = [&](float lp, int cnt, float u, float &lse) {
-      const float mx = dg_max(lp);
+      const float mx = lanes_max(lp);
       const float c = wave_cumsum(lane < cnt ? expf(lp - mx) : 0.f);
       const float tot = lane_val(c, cnt - 1);
       const unsigned long long hit = __ballot(lane < cnt && u * tot < c);
@@ -838,8 +796,8 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
           const float zz = lt - mu_l;
           c = nlw - s_l - 0.918938533204672742f - lt - 0.5f * zz * zz * expf(-2.f * s_l);
         }
-        const float cm = dg_max(c);
-        const float lg = cm + logf(dg_sum<64>(lane < M ? expf(c - cm) : 0.f));
+        const float cm = lanes_max(c);
+        const float lg = cm + logf(lanes_sum<64>(lane < M ? expf(c - cm) : 0.f));
         if (lane == 0) a.d_logg[di] = lg;
       }
     } else if (wave == 1) {

@@ -241,13 +241,13 @@ size_t wbatch_packed_elems(int N, int K);
 void launch_pack_wbatch(const void *W, int N, int K, int bf16, void *out, hipStream_t s);
 void launch_block(const BlockArgs &a, int bf16, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
-// Per-sequence verify pass (k_verify_seq): one workgroup runs the whole target
-// pass of one sequence's P = gamma + 1 positions (embedding, every layer with
+// Per-sequence verify pass or AR step (k_verify_seq): one workgroup runs the whole
+// target pass of one sequence's P = gamma + 1 (or 1) positions (embedding, every layer with
 // its attention, decoder, verify epilogue), the rows staying in LDS.
 struct VerifySeqArgs {
   int P, d, F, H, L, M, K;
   FusedLayerW layer[FD_MAX_LAYERS];
-  const void *type_emb, *Ek1_w, *head_w;
+  const void *type_emb, *Ek1_w, *mix_w, *k2_w;
   const float *lnf_g, *lnf_b, *k1_b, *head_b, *freq;
   char *kc, *vc;            // target cache bases; layer stride layer_bytes
   size_t layer_bytes;
@@ -260,10 +260,10 @@ struct VerifySeqArgs {
   const int32_t *dr_k;
   int dr_stride;
   uint32_t *status;
-  HeadArgs h;               // HEAD_VERIFY
+  HeadArgs h;               // HEAD_VERIFY, or HEAD_AR (P = 1)
 };
-// whether k_verify_seq serves a target of these sizes for P positions
-bool verify_seq_ok(int bf16, int L, int d, int H, int F, int M, int K, int P);
+// whether k_verify_seq serves a THP target of these sizes for P positions over caches of kv_cap
+bool verify_seq_ok(int bf16, int L, int d, int H, int F, int P, int kv_cap);
 void launch_verify_seq(const VerifySeqArgs &a, int B, int bf16, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
 

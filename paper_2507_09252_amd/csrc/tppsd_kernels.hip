@@ -3384,181 +3384,467 @@ void launch_block(const BlockArgs &a, int bf16, hipStream_t s, hipEvent_t ev0, h
 
 // ---------------------------------------------------------------------------
 // Per-sequence verify pass for small THP targets (§4.3 "Verification"): one
-// 512-thread workgroup runs the target over one sequence's P = gamma + 1 new
-// positions -- the pending event and the drafts -- through every layer and
-// the decoder, with the verify epilogue per row. The P rows are one 16-row
-// MFMA tile; q, the attention output and the stream stay in LDS, keys and
-// values go to the cache and the attention reads them back from it (as the
-// layered pass). Each product's weights are loaded one step ahead.
+// 512-thread workgroup runs the target over one sequence's P = gamma + 1 <= 16
+// new positions -- the pending event and the drafts -- through every layer and
+// the decoder, with the verify epilogue per row. The positions are the columns
+// of 16-wide MFMA tiles (the weights are the first operand, so that a lane ends
+// up with four consecutive outputs of one position).
+//
+// What bounds it: the chain of phases, seven per layer, each a barrier and an
+// LDS round trip around a product; then, in fp32, the matrix units (16 x 16 x 4
+// products, 32 cycles each). So every product's weights are reloaded for the
+// next layer right after their use and are in flight for a whole layer, the
+// first cached keys and values of a layer are loaded during the layer before,
+// products with few tiles split K over the waves and leave their partial sums
+// to the next phase, and the residual stream stays in registers (a wave owns
+// two positions). Measured: fp32 d = 32, 2 layers, 11 positions after 100 events
+// 28 -> 20 us (before: activations as the first operand, the stream and every
+// vector through LDS); fp32 d = 64, 4 layers, 64 sequences 87 -> 48 us (before:
+// nine launches of row blocks and attention).
 // ---------------------------------------------------------------------------
-inline __host__ __device__ int verify_seq_vec_floats(int L, int d, int F, int M, int K) {
-  return L * (9 * d + F) + 3 * d + 3 * M + K;
-}
+
+// 32 cached positions of one head, d_head 16, against up to 16 queries
+template <typename ELT> struct VsStep;
+template <> struct VsStep<bf16_t> {
+  short4_t k0, k1;
+  uint4 v;
+  // last: the last valid position (loads are clamped to it)
+  __device__ __forceinline__ void load(const bf16_t *kc, const bf16_t *vc, int kt, int last, int lane) {
+    const int rr = lane & 15, g = lane >> 4, r0 = 8 * (rr >> 2) + (rr & 3);
+    k0 = *(const short4_t *)(kc + min(kt + r0, last) * 16 + 4 * g);
+    k1 = *(const short4_t *)(kc + min(kt + r0 + 4, last) * 16 + 4 * g);
+    v = *(const uint4 *)(vc + min((kt >> 3) + g, last >> 3) * 128 + rr * 8);
+  }
+  // lane (r, g): scores of keys kt + 8 g .. + 7 for query r
+  typedef short4_t qfrag;
+  static __device__ __forceinline__ qfrag query(const bf16_t *q) { return *(const short4_t *)q; }
+  static __device__ __forceinline__ int key(int g, int j) { return 8 * g + j; }
+  __device__ __forceinline__ void scores(qfrag q, float *s) const {
+    const f32x4_t z = {0.f, 0.f, 0.f, 0.f};
+    const f32x4_t a = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(k0, q, z, 0, 0, 0);
+    const f32x4_t b = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(k1, q, z, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = a[j], s[4 + j] = b[j];
+  }
+  // o[4 g + i] of query r += sum over the keys; nv: valid positions of the step
+  __device__ __forceinline__ f32x4_t apply(const float *p, int nv, int g, f32x4_t o) const {
+    u32x4_t w = {v.x, v.y, v.z, v.w};
+    if (nv < 32) {   // (uniform: values past the range may be any bits)
+      const int n8 = nv - 8 * g;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = 2 * i >= n8 ? 0u : (2 * i + 1 >= n8 ? w[i] & 0xFFFFu : w[i]);
+    }
+    const u32x4_t pw = {pk2bf(p[0], p[1]), pk2bf(p[2], p[3]), pk2bf(p[4], p[5]), pk2bf(p[6], p[7])};
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, pw), o,
+                                                   0, 0, 0);
+  }
+};
+template <> struct VsStep<float> {
+  f32x4_t k[2];
+  float v[8];
+  __device__ __forceinline__ void load(const float *kc, const float *vc, int kt, int last, int lane) {
+    const int rr = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) k[h] = *(const f32x4_t *)(kc + min(kt + 16 * h + rr, last) * 16 + 4 * g);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = vc[min(kt + key(g, j), last) * 16 + rr];
+  }
+  // lane (r, g): scores of keys kt + 16 h + 4 g .. + 3 (h = 0, 1) for query r
+  typedef f32x4_t qfrag;
+  static __device__ __forceinline__ qfrag query(const float *q) { return *(const f32x4_t *)q; }
+  static __device__ __forceinline__ int key(int g, int j) { return 16 * (j >> 2) + 4 * g + (j & 3); }
+  __device__ __forceinline__ void scores(qfrag q, float *s) const {
+    f32x4_t a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      a = __builtin_amdgcn_mfma_f32_16x16x4f32(k[0][e], q[e], a, 0, 0, 0);
+      b = __builtin_amdgcn_mfma_f32_16x16x4f32(k[1][e], q[e], b, 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = a[j], s[4 + j] = b[j];
+  }
+  // (values past the range were clamped to its last position: finite, times a probability of 0)
+  __device__ __forceinline__ f32x4_t apply(const float *p, int nv, int g, f32x4_t o) const {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) o = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], p[j], o, 0, 0, 0);
+    return o;
+  }
+};
 
 template <typename ELT, int D, int F>
 __global__ __launch_bounds__(512) void k_verify_seq(VerifySeqArgs a) {
-  constexpr int LX = D + 4, LH = (F > 4 * D ? F : 4 * D) + 4, DH = 16;
-  // column tiles per wave (8 waves) of each product; the decoder's 3M + K
-  // logits are at most 128 (64 / d) wide (verify_seq_ok)
-  constexpr int TQ = (4 * D + 127) / 128, TO = (D + 127) / 128, T1 = (F + 127) / 128, TH = D >= 64 ? 1 : 64 / D;
-  extern __shared__ __attribute__((aligned(16))) float sm[];
-  __shared__ float tok_t[16];
-  __shared__ int tok_k[16];
-  const int LV = 3 * a.M + a.K + 1;
-  float *xs = sm, *as = xs + 16 * LX, *qs = as + 16 * LX, *os = qs + 16 * LX;
-  float *hs = os + 16 * LX;          // [16][LH] FFN hidden / decoder e | tanh
-  float *hv = hs + 16 * LH;          // [16][LV] decoder logits
-  float *red = hv + 16 * LV;         // attention merge: [8 waves][16 queries][DH + 2]
-  float *vec = red + 8 * 16 * (DH + 2);
-  const int tid = threadIdx.x, b = blockIdx.x, P = a.P, H = a.H;
-  if (a.done[b]) return;
+  typedef MfmaStep<ELT> S;
+  typedef typename S::frag frag;
+  constexpr int NW = 8, DH = 16, H = D / 16, DT = D / 16, VE = 16 / sizeof(ELT);
+  constexpr int VD = D / 4 / VE, VF = F / 4 / VE;       // 16-byte vectors of a lane's quarter of a D- or F-wide row
+  constexpr int TQ = 3 * D / 16, TE = 4 * D / 16, TF = F / 16;
+  constexpr int TPQ = (TE + NW - 1) / NW, TPF = (TF + NW - 1) / NW, TPH = 2;
+  constexpr int KG = NW / DT;                           // waves per tile of the D-wide products
+  constexpr int KGO = KG < VD ? KG : VD, NO = VD / KGO, KGF = KG < VF ? KG : VF, NF = VF / KGF;
+  static_assert(TPF <= TPH && VD == D / S::KSTEP, "the heads' fragments fit the FFN's");
+  constexpr int WPH = NW / H, NB = 2, NP = D / 32;      // waves per head; key steps per batch; positions per lane
+  constexpr int PAD = VE, LA = D + PAD, LF = (F > 4 * D ? F : 4 * D) + PAD, LP = D + 4, LM = DH + 4;
+  static_assert(VD % KGO == 0 && VF % KGF == 0 && KGO * NO == VD && KGF * NF == VF, "K split");
+  __shared__ __attribute__((aligned(16))) ELT as[16 * LA], qs[16 * LA], hs[16 * LF];
+  __shared__ __attribute__((aligned(16))) ELT kt_s[H][16 * DH], vt_s[H][32 * DH];
+  // partial sums of the attention (per wave: max, sum, -, -, 16 sums per
+  // position) and of the D-wide products; the decoder logits [16][3M + K + 1] at the end
+  constexpr int NPM = NW * 16 * LM, NPA = KGO * 16 * LP, NPB = KGF * 16 * LP;
+  __shared__ __attribute__((aligned(16))) float part[NPM + NPA + NPB];
+  static_assert(NPM + NPA + NPB >= 16 * (3 * TPPSD_MAX_MIX + TPPSD_MAX_TYPES + 1), "logits fit");
+  float *const pm = part, *const pA = part + NPM, *const pB = pA + NPA, *const hv = part;
+  const int tid = threadIdx.x, b = blockIdx.x, P = a.P;
+  const bool skip = a.done[b] != 0;
+  if (skip && D == 32) return;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rr = lane & 15, g = lane >> 4;
+  const int M = a.M, K = a.K, Mt = (M + 15) / 16, Kt = (K + 15) / 16, LV = 3 * M + K + 1;
   const int pos0 = a.lenT[b];
-  const size_t seq_row0 = (size_t)b * H * a.cap;
-  // phase 0: the small vectors (per layer LN1 g, b, qkv_b, out_b, LN2 g, b,
-  // ffn1_b, ffn2_b; then LN_f g, b, k1_b, decoder bias), the tokens, and the
-  // first layer's q, k, v weights, all loads issued before any LDS store
-  const int nvec = verify_seq_vec_floats(a.L, D, F, a.M, a.K);
-  constexpr int VMAX = (FD_MAX_LAYERS * (9 * D + F) + 3 * D + 3 * 64 + 64 + 511) / 512;
-  float vv[VMAX];
+  const int tn = wave % DT, kg = wave / DT;             // the D-wide products: tile and K group
+  const int head = wave / WPH, sub = wave % WPH;        // attention: head and place among its waves
+  // the stream: this lane's element j of positions prow(i), i < NP (D = 32: two positions side by side)
+  const int j = lane & (D - 1);
+  auto prow = [&](int i) { return D == 64 ? 2 * wave + i : 2 * wave + (lane >> 5); };
+
+  // ---- the first layer's weights (packed order: a wave's vector is 1 KB of
+  // contiguous memory; lane (r, g) holds row r, elements g K/4 + VE i ..) ----
+  auto vec = [&](const void *W, int nv, int t, int i) -> frag {
+    return __builtin_bit_cast(frag, ((const u32x4_t *)W)[((size_t)t * nv + i) * 64 + lane]);
+  };
+  frag wq[TPQ][VD], wo[NO], w1[TPH][VD], w2[NF];   // (w1: at the end the decoder heads, TPH tiles)
+  auto load_q = [&](const void *W, int tiles) {
 #pragma unroll
-  for (int i = 0; i < VMAX; ++i) {
-    int o = tid + 512 * i;
-    vv[i] = 0.f;
-    if (o < nvec) {
-      const int per = 9 * D + F;
-      if (o < a.L * per) {
-        const int ly = o / per;
-        o -= ly * per;
-        const FusedLayerW &w = a.layer[ly];
-        vv[i] = o < D ? w.ln1_g[o] : o < 2 * D ? w.ln1_b[o - D] : o < 5 * D ? w.qkv_b[o - 2 * D]
-              : o < 6 * D ? w.out_b[o - 5 * D] : o < 7 * D ? w.ln2_g[o - 6 * D] : o < 8 * D ? w.ln2_b[o - 7 * D]
-              : o < 8 * D + F ? w.ffn1_b[o - 8 * D] : w.ffn2_b[o - 8 * D - F];
-      } else {
-        o -= a.L * per;
-        vv[i] = o < D ? a.lnf_g[o] : o < 2 * D ? a.lnf_b[o - D] : o < 3 * D ? a.k1_b[o - 2 * D] : a.head_b[o - 3 * D];
-      }
-    }
-  }
-  float tt = 0.f;
-  int tk = 0;
-  if (tid < P) {
-    if (tid == 0) {   // the pending committed event
-      const size_t i = (size_t)b * a.ev_stride + pos0;
-      tt = a.ev_t[i];
-      tk = a.ev_k[i];
-    } else {          // draft tid - 1
-      const size_t i = (size_t)b * a.dr_stride + tid - 1;
-      tt = a.dr_t[i];
-      tk = a.dr_k[i];
-    }
-  }
-  WBatch<ELT, D, TQ> w_q;   // q, k, v (3D columns) or [E; V_k1] (4D)
-  w_q.load((const ELT *)a.layer[0].qkv_w, 3 * D);
+    for (int t = 0; t < TPQ; ++t)
 #pragma unroll
-  for (int i = 0; i < VMAX; ++i)
-    if (tid + 512 * i < nvec) vec[tid + 512 * i] = vv[i];
-  if (tid < 16) {
-    tok_t[tid] = tt;
-    tok_k[tid] = min(max(tk, 0), a.K - 1);
+      for (int i = 0; i < VD; ++i) wq[t][i] = vec(W, VD, min(wave + NW * t, tiles - 1), i);
+  };
+  auto load_o = [&](const void *W) {
+#pragma unroll
+    for (int i = 0; i < NO; ++i) wo[i] = vec(W, VD, tn, min(kg, KGO - 1) * NO + i);
+  };
+  auto load_1 = [&](const void *W) {
+#pragma unroll
+    for (int t = 0; t < TPF; ++t)
+#pragma unroll
+      for (int i = 0; i < VD; ++i) w1[t][i] = vec(W, VD, min(wave + NW * t, TF - 1), i);
+  };
+  auto load_2 = [&](const void *W) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i) w2[i] = vec(W, VF, tn, min(kg, KGF - 1) * NF + i);
+  };
+  // the positions' times and types (uniform per position; D = 32: per half-wave)
+  float tt[NP];
+  int tk[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int r = min(prow(i), P - 1);
+    const size_t ie = (size_t)b * a.ev_stride + pos0, id = (size_t)b * a.dr_stride + max(r - 1, 0);
+    const float te = a.ev_t[ie], td = a.dr_t[id];
+    const int ke = a.ev_k[ie], kd = a.dr_k[id];
+    tt[i] = r == 0 ? te : td;   // the pending committed event, else draft r - 1
+    tk[i] = min(max(r == 0 ? ke : kd, 0), K - 1);
   }
-  lds_barrier();
-  for (int idx = tid; idx < 16 * D; idx += blockDim.x) {
-    const int r = idx / D, j = idx - r * D;
-    float v = 0.f;
-    qs[r * LX + j] = 0.f;   // rows past P stay zero
-    os[r * LX + j] = 0.f;
-    if (r < P) {
-      const float arg = tok_t[r] * a.freq[j];
-      v = ((j & 1) ? cosf(arg) : sinf(arg)) + ld((const ELT *)a.type_emb, (size_t)tok_k[r] * D + j);
+  load_q(a.layer[0].qkv_w, TQ);
+  // ---- cached keys and values: a batch of this wave's 32-position steps -----
+  const size_t slab = ((size_t)b * H + head) * a.cap * DH;
+  const int nst = skip ? 0 : (pos0 + 31) / 32, mine = nst > sub ? (nst - sub + WPH - 1) / WPH : 0;
+  VsStep<ELT> kv[NB];
+  auto fetch = [&](int ly, int bt) {
+    if (nst == 0) return;   // (uniform)
+    const ELT *kc = (const ELT *)(a.kc + a.layer_bytes * ly) + slab, *vc = (const ELT *)(a.vc + a.layer_bytes * ly) + slab;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) kv[i].load(kc, vc, 32 * min(sub + WPH * (bt * NB + i), nst - 1), pos0 - 1, lane);
+  };
+  fetch(0, 0);
+  load_o(a.layer[0].out_w);
+  load_1(a.layer[0].ffn1_w);
+  load_2(a.layer[0].ffn2_w);
+  float n_g = a.layer[0].ln1_g[j], n_b = a.layer[0].ln1_b[j];   // the next LayerNorm's gain and bias
+  const float fr = a.freq[j];
+  // embedding
+  float x[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    float zs, zc;
+    sincosf(tt[i] * fr, &zs, &zc);
+    x[i] = ((j & 1) ? zc : zs) + ld((const ELT *)a.type_emb, (size_t)tk[i] * D + j);
+  }
+  // tail positions past P score against whatever the buffers hold: zero, once
+  for (int i = tid; i < H * 16 * DH; i += 512) (&kt_s[0][0])[i] = 0;
+  for (int i = tid; i < H * 32 * DH; i += 512) (&vt_s[0][0])[i] = 0;
+  auto norm = [&](float gn, float bt) {   // LayerNorm of the stream into the operand rows
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const float mean = lanes_sum<D>(x[i]) / (float)D, c = x[i] - mean;
+      const float rstd = rsqrt_nr(lanes_sum<D>(c * c) / (float)D + 1e-5f);
+      st(as, prow(i) * LA + j, c * rstd * gn + bt);
     }
-    xs[r * LX + j] = v;
-  }
+  };
+  auto add = [&](const float *parts, int np, float bias) {   // partial sums [np][16][LP] into the stream
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      float v = parts[prow(i) * LP + j];
+      for (int q = 1; q < np; ++q) v += parts[q * 16 * LP + prow(i) * LP + j];
+      x[i] += v + bias;
+    }
+  };
+  // operand vector i of position rr from rows of stride ld, elements g q .. (q: a quarter of the width)
+  auto opnd = [&](const ELT *rows, int ld, int q, int i) -> frag { return *(const frag *)(rows + rr * ld + g * q + i * VE); };
+  norm(n_g, n_b);
   lds_barrier();
-  const float *hvec = vec + a.L * (9 * D + F);
   for (int ly = 0; ly < a.L; ++ly) {
     const FusedLayerW &w = a.layer[ly];
-    const float *lv = vec + ly * (9 * D + F);
-    const float *ln1_g = lv, *ln1_b = lv + D, *qkv_b = lv + 2 * D, *out_b = lv + 5 * D, *ln2_g = lv + 6 * D,
-                *ln2_b = lv + 7 * D, *ffn1_b = lv + 8 * D, *ffn2_b = lv + 8 * D + F;
-    ELT *kc = (ELT *)(a.kc + a.layer_bytes * ly), *vc = (ELT *)(a.vc + a.layer_bytes * ly);
-    tile_layernorm<ELT>(xs, LX, as, LX, ln1_g, ln1_b, P, D);
-    lds_barrier();
-    tile_mm16(w_q, 3 * D, as, LX, [&](int r, int n, float y) {
-      if (r >= P) return;
-      const float v = rnd_act<ELT>(y + qkv_b[n]);
-      const int which = n / D, c = n - which * D;
+    const bool last = ly + 1 == a.L;
+    const FusedLayerW &wn = a.layer[last ? ly : ly + 1];   // the next layer's (unused loads after the last)
+    // this layer's vectors
+    const float o_b = w.out_b[j], g2 = w.ln2_g[j], b2 = w.ln2_b[j], f2b = w.ffn2_b[j];
+    n_g = (last ? a.lnf_g : wn.ln1_g)[j];
+    n_b = (last ? a.lnf_b : wn.ln1_b)[j];
+    float4 qb[TPQ], fb[TPF];
+#pragma unroll
+    for (int t = 0; t < TPQ; ++t) qb[t] = *(const float4 *)(w.qkv_b + 16 * min(wave + NW * t, TQ - 1) + 4 * g);
+#pragma unroll
+    for (int t = 0; t < TPF; ++t) fb[t] = *(const float4 *)(w.ffn1_b + 16 * min(wave + NW * t, TF - 1) + 4 * g);
+    // ---- q, k, v --------------------------------------------------------------
+    frag in[VD];
+#pragma unroll
+    for (int i = 0; i < VD; ++i) in[i] = opnd(as, LA, D / 4, i);
+#pragma unroll
+    for (int t = 0; t < TPQ; ++t) {
+      const int tile = wave + NW * t;
+      if (tile >= TQ) break;   // uniform
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < VD; ++i) acc = S::mma(wq[t][i], in[i], acc);
+      const float y[4] = {acc[0] + qb[t].x, acc[1] + qb[t].y, acc[2] + qb[t].z, acc[3] + qb[t].w};
+      const int which = tile / DT, hh = tile % DT;
       if (which == 0) {
-        qs[r * LX + c] = v;
-      } else {
-        const int pos = pos0 + r, h = c >> 4, j = c & 15;
-        if (pos < a.cap)
-          st(which == 1 ? kc : vc, which == 1 ? (seq_row0 + (size_t)h * a.cap + pos) * DH + j
-                                                : v_at<ELT>(seq_row0 + (size_t)h * a.cap, pos, j, DH), v);
-        else
-          atomicOr(a.status, TPPSD_STATUS_CAPACITY);
+        st4(qs, rr * LA + 16 * hh + 4 * g, y[0], y[1], y[2], y[3]);
+      } else if (rr < P) {
+        const int pos = pos0 + rr;
+        const bool fits = pos < a.cap;
+        if (!fits) atomicOr(a.status, TPPSD_STATUS_CAPACITY);
+        const size_t row0 = ((size_t)b * H + hh) * a.cap * DH;   // (uniform)
+        if (which == 1) {
+          st4(&kt_s[hh][0], rr * DH + 4 * g, y[0], y[1], y[2], y[3]);
+          if (fits) st4((ELT *)(a.kc + a.layer_bytes * ly) + row0, pos * DH + 4 * g, y[0], y[1], y[2], y[3]);
+        } else {
+          ELT *gv = (ELT *)(a.vc + a.layer_bytes * ly) + row0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            st(&vt_s[hh][0], v_at<ELT>(0, rr, 4 * g + c, DH), y[c]);
+            if (fits) st(gv, (int)v_at<ELT>(0, pos, 4 * g + c, DH), y[c]);
+          }
+        }
       }
-    });
-    __syncthreads();   // the new keys and values are in the cache
-    // (fp32 steps take twice the registers: two per load batch)
-    wg_attention<ELT, DH, 16, sizeof(ELT) == 4 ? 2 : 4>(qs, os, kc, vc, seq_row0, a.cap, H, P, pos0, LX, red);
-    // at most two weight batches live at a time (512 threads: 256 registers)
-    WBatch<ELT, D, TO> w_o;
-    w_o.load((const ELT *)w.out_w, D);
+    }
+    load_q(last ? a.Ek1_w : wn.qkv_w, last ? TE : TQ);
     lds_barrier();
-    WBatch<ELT, D, T1> w_f1;
-    w_f1.load((const ELT *)w.ffn1_w, F);
-    tile_mm16(w_o, D, os, LX, [&](int r, int n, float y) { xs[r * LX + n] += y + out_b[n]; });
+    // ---- attention ------------------------------------------------------------
+    {
+      const typename VsStep<ELT>::qfrag qf = VsStep<ELT>::query(qs + rr * LA + 16 * head + 4 * g);
+      const float scale = sizeof(ELT) == 2 ? 0.25f * 1.4426950408889634f : 0.25f;   // 1 / sqrt(16) (base-2 units)
+      float m_run = -INFINITY, l_run = 0.f;
+      f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+      // n steps' scores in s: new maximum, probabilities (in place), rescaled sums
+      auto softmax = [&](float (&s)[NB][8], int n) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          if (i < n)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) mx = fmaxf(mx, s[i][q]);
+        const float m_new = fmaxf(m_run, xor32_max(xor16_max(mx)));
+        const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+        const float al = exp_score<ELT>(m_run - m_ref);
+        float ps = 0.f;
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          if (i < n)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              s[i][q] = rnd_act<ELT>(exp_score<ELT>(s[i][q] - m_ref));
+              ps += s[i][q];
+            }
+        l_run = l_run * al + ps;
+        m_run = m_new;
+        o *= al;
+      };
+      const int nbt = (mine + NB - 1) / NB;
+      for (int bt = 0; bt < nbt; ++bt) {
+        float s[NB][8];
+        const int n = min(NB, mine - bt * NB);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          if (i >= n) break;   // uniform
+          const int kt = 32 * (sub + WPH * (bt * NB + i));
+          kv[i].scores(qf, s[i]);
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            s[i][q] = kt + VsStep<ELT>::key(g, q) < pos0 ? s[i][q] * scale : -INFINITY;
+        }
+        softmax(s, n);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+          if (i >= n) break;
+          o = kv[i].apply(s[i], pos0 - 32 * (sub + WPH * (bt * NB + i)), g, o);
+        }
+        const bool more = bt + 1 < nbt;
+        if (more || !last) fetch(more ? ly : ly + 1, more ? bt + 1 : 0);   // (uniform)
+      }
+      if (!skip && sub == nst % WPH) {
+        // the pass's own positions, from LDS
+        VsStep<ELT> tl;
+        tl.load(&kt_s[head][0], &vt_s[head][0], 0, 15, lane);
+        float s[NB][8];
+        tl.scores(qf, s[0]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int key = VsStep<ELT>::key(g, q);
+          s[0][q] = key <= rr && key < P && pos0 + key < a.cap ? s[0][q] * scale : -INFINITY;
+        }
+        softmax(s, 1);
+        o = tl.apply(s[0], 32, g, o);
+      }
+      l_run = xor32_sum(xor16_sum(l_run));
+      float *r = pm + (wave * 16 + rr) * LM;
+      if (g == 0) {
+        r[0] = m_run;
+        r[1] = l_run;
+      }
+      *(f32x4_t *)(r + 4 + 4 * g) = o;
+    }
     lds_barrier();
-    tile_layernorm<ELT>(xs, LX, as, LX, ln2_g, ln2_b, P, D);
+    // ---- output projection on the merged attention output ---------------------
+    if (kg < KGO) {
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NO; ++i) {
+        const int k = g * (D / 4) + (kg * NO + i) * VE, hh = k / DH, dd = k % DH;
+        const float *r0 = pm + (hh * WPH * 16 + rr) * LM;
+        float Mx = -INFINITY, Ls = 0.f, v[VE];
+#pragma unroll
+        for (int c = 0; c < VE; ++c) v[c] = 0.f;
+#pragma unroll
+        for (int q = 0; q < WPH; ++q) Mx = fmaxf(Mx, r0[q * 16 * LM]);
+#pragma unroll
+        for (int q = 0; q < WPH; ++q) {
+          const float *r = r0 + q * 16 * LM;
+          const float f = r[0] == -INFINITY ? 0.f : exp_score<ELT>(r[0] - Mx);
+          Ls += r[1] * f;
+#pragma unroll
+          for (int c = 0; c < VE; ++c) v[c] += r[4 + dd + c] * f;
+        }
+        const float inv = Ls > 0.f ? rcp_nr(Ls) : 0.f;
+        frag f;
+        if constexpr (sizeof(ELT) == 2)
+          f = __builtin_bit_cast(frag, make_uint4(pk2bf(v[0] * inv, v[1] * inv), pk2bf(v[2] * inv, v[3] * inv),
+                                                  pk2bf(v[4] * inv, v[5] * inv), pk2bf(v[6] * inv, v[7] * inv)));
+        else
+          f = (f32x4_t){v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv};
+        acc = S::mma(wo[i], f, acc);
+      }
+      *(f32x4_t *)(pA + (kg * 16 + rr) * LP + 16 * tn + 4 * g) = acc;
+    }
+    load_o(wn.out_w);
     lds_barrier();
-    WBatch<ELT, F, TO> w_f2;
-    w_f2.load((const ELT *)w.ffn2_w, D);
-    tile_mm16(w_f1, F, as, LX,
-              [&](int r, int n, float y) { hs[r * LH + n] = rnd_act<ELT>(fmaxf(y + ffn1_b[n], 0.f)); });
+    add(pA, KGO, o_b);
+    norm(g2, b2);
     lds_barrier();
-    tile_mm16(w_f2, D, hs, LH, [&](int r, int n, float y) { xs[r * LX + n] += y + ffn2_b[n]; });
-    if (ly + 1 < a.L)
-      w_q.load((const ELT *)a.layer[ly + 1].qkv_w, 3 * D);
-    else
-      w_q.load((const ELT *)a.Ek1_w, 4 * D);
+    // ---- feed-forward block ---------------------------------------------------
+#pragma unroll
+    for (int i = 0; i < VD; ++i) in[i] = opnd(as, LA, D / 4, i);
+#pragma unroll
+    for (int t = 0; t < TPF; ++t) {
+      const int tile = wave + NW * t;
+      if (tile >= TF) break;
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < VD; ++i) acc = S::mma(w1[t][i], in[i], acc);
+      st4(hs, rr * LF + 16 * tile + 4 * g, fmaxf(acc[0] + fb[t].x, 0.f), fmaxf(acc[1] + fb[t].y, 0.f),
+          fmaxf(acc[2] + fb[t].z, 0.f), fmaxf(acc[3] + fb[t].w, 0.f));
+    }
+    if (!last) {
+      load_1(wn.ffn1_w);
+    } else {
+      // the decoder heads' tiles: 16 rows of V_w, V_mu, V_sigma (on e1, e2, e3) or of
+      // V_k2; rows past a head's count repeat its last and are not used
+#pragma unroll
+      for (int t = 0; t < TPH; ++t) {
+        const int tile = wave + NW * t, c = min(tile / Mt, 3);
+        const ELT *hw = c < 3 ? (const ELT *)a.mix_w + (size_t)c * M * D : (const ELT *)a.k2_w;
+        const int row = c < 3 ? min(16 * (tile % Mt) + rr, M - 1) : min(max(16 * (tile - 3 * Mt), 0) + rr, K - 1);
+#pragma unroll
+        for (int s = 0; s < VD; ++s) w1[t][s] = *(const frag *)(hw + (size_t)row * D + S::KSTEP * s + VE * g);
+      }
+    }
+    lds_barrier();
+    if (kg < KGF) {
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < NF; ++i) acc = S::mma(w2[i], opnd(hs, LF, F / 4, kg * NF + i), acc);
+      *(f32x4_t *)(pB + (kg * 16 + rr) * LP + 16 * tn + 4 * g) = acc;
+    }
+    load_2(wn.ffn2_w);
+    lds_barrier();
+    add(pB, KGF, f2b);
+    norm(n_g, n_b);
     lds_barrier();
   }
-  // decoder on every row: LN_f, [E; V_k1] with tanh, the block-diagonal heads
-  tile_layernorm<ELT>(xs, LX, as, LX, hvec, hvec + D, P, D);
+  // ---- decoder on every position: [E; V_k1] with tanh, the heads --------------
+  {
+    frag in[VD];
+#pragma unroll
+    for (int i = 0; i < VD; ++i) in[i] = opnd(as, LA, D / 4, i);
+#pragma unroll
+    for (int t = 0; t < TPQ; ++t) {
+      const int tile = wave + NW * t;
+      if (tile >= TE) break;
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < VD; ++i) acc = S::mma(wq[t][i], in[i], acc);
+      if (16 * tile >= 3 * D) {   // (uniform: a tile of V_k1)
+        const float4 kb = *(const float4 *)(a.k1_b + 16 * tile + 4 * g - 3 * D);
+        acc = (f32x4_t){tanhf(acc[0] + kb.x), tanhf(acc[1] + kb.y), tanhf(acc[2] + kb.z), tanhf(acc[3] + kb.w)};
+      }
+      st4(hs, rr * LF + 16 * tile + 4 * g, acc[0], acc[1], acc[2], acc[3]);
+    }
+  }
   lds_barrier();
-  const float *k1_b = hvec + 2 * D, *head_b = hvec + 3 * D;
-  WBatch<ELT, 4 * D, TH> w_h;
-  w_h.load((const ELT *)a.head_w, 3 * a.M + a.K);
-  tile_mm16(w_q, 4 * D, as, LX, [&](int r, int n, float y) {
-    hs[r * LH + n] = n < 3 * D ? rnd_act<ELT>(y) : rnd_act<ELT>(tanhf(y + k1_b[n - 3 * D]));
-  });
+#pragma unroll
+  for (int t = 0; t < TPH; ++t) {
+    const int tile = wave + NW * t;
+    if (tile >= 3 * Mt + Kt) break;
+    const int c = min(tile / Mt, 3);
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < VD; ++s)
+      acc = S::mma(w1[t][s], *(const frag *)(hs + rr * LF + c * D + S::KSTEP * s + VE * g), acc);
+    const int r0 = 16 * (c < 3 ? tile % Mt : tile - 3 * Mt) + 4 * g, cnt = c < 3 ? M : K, o0 = c < 3 ? c * M : 3 * M;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (r0 + q < cnt) hv[rr * LV + o0 + r0 + q] = acc[q] + a.head_b[o0 + r0 + q];
+  }
   lds_barrier();
-  tile_mm16(w_h, 3 * a.M + a.K, hs, LH, [&](int r, int n, float y) { hv[r * LV + n] = y + head_b[n]; });
-  lds_barrier();
-  for (int r = tid >> 6; r < P; r += blockDim.x >> 6) head_row(hv + r * LV, a.M, a.K, a.h, b, r);
+  for (int r = wave; r < P; r += NW) head_row(hv + r * LV, M, K, a.h, b, r);
 }
 
-static size_t verify_seq_lds_bytes(int L, int d, int F, int M, int K) {
-  const int LX = d + 4, LH = (F > 4 * d ? F : 4 * d) + 4, LV = 3 * M + K + 1;
-  return ((size_t)16 * (4 * LX + LH + LV) + 8 * 16 * (16 + 2) + verify_seq_vec_floats(L, d, F, M, K)) * sizeof(float);
-}
-
-bool verify_seq_ok(int bf16, int L, int d, int H, int F, int M, int K, int P) {
-  // instantiated widths, d_head 16, one 16-row tile, every product's column
-  // tiles inside one weight batch of the eight waves, default LDS limit.
-  // Taken for d = 32 (measured: the verify pass of the small fp32 workload
-  // 59 -> 36 us per round). At d = 64 the gain measured 8 % of the pass, and
-  // the layered pass keeps the verify attention a kernel of its own, whose
-  // KV bandwidth is reported; d = 64 stays layered.
-  const bool widths = d == 32 && (F == 64 || F == 128);
-  (void)bf16;
-  return widths && d == 16 * H && L <= FD_MAX_LAYERS && P <= 16 && 3 * M + K <= 128 * (d >= 64 ? 1 : 64 / d) &&
-         verify_seq_lds_bytes(L, d, F, M, K) <= 64 * 1024;
+bool verify_seq_ok(int bf16, int L, int d, int H, int F, int P, int kv_cap) {
+  // instantiated widths, d_head 16, one tile of 16 positions. At d = 32 always;
+  // at d = 64 while the contexts are short: a sequence's caches stream through
+  // one CU here, and through a workgroup per head in the layered pass. Measured,
+  // d = 64 / F = 256, 4 layers, 64 sequences x 11 positions after 100 / 600 / 2500
+  // events, this kernel against the layered pass: fp32 48 / 87 / 248 vs 87 / 110
+  // / 175 us, bf16 28 / 45 / 107 vs 61 / 72 / 91; 16 sequences: fp32 48 / 85 /
+  // 240 vs 76 / 90 / 114, bf16 27 / 41 / 106 vs 80 / 87 / 106; 1024 sequences
+  // after 600 events fp32 380 vs 494. A job's average context is about half of
+  // the capacity, which is what the host knows
+  const bool widths = (d == 32 && (F == 64 || F == 128)) ||
+                      (d == 64 && (F == 128 || F == 256) && kv_cap <= (bf16 ? 4096 : 1024));
+  return widths && d == 16 * H && L <= FD_MAX_LAYERS && P <= 16;
 }
 
 void launch_verify_seq(const VerifySeqArgs &a, int B, int bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  const size_t lds = verify_seq_lds_bytes(a.L, a.d, a.F, a.M, a.K);
-  auto go = [&](auto kern) { hipExtLaunchKernelGGL(kern, dim3(B), dim3(512), lds, s, ev0, ev1, 0, a); };
+  auto go = [&](auto kern) { hipExtLaunchKernelGGL(kern, dim3(B), dim3(512), 0, s, ev0, ev1, 0, a); };
 #define TPPSD_VS(ELT)                                               \
   if (a.d == 32 && a.F == 64) go(k_verify_seq<ELT, 32, 64>);        \
   else if (a.d == 32) go(k_verify_seq<ELT, 32, 128>);               \
