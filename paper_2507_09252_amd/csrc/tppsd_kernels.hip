@@ -716,10 +716,16 @@ __global__ __launch_bounds__(256) void k_gemm_lds(const ELT *__restrict__ X, con
 // workgroup) go straight from global memory into MFMA operand registers.
 // Rounding points are the layered kernels': LayerNorm outputs and hidden
 // activations are bf16, products accumulate in fp32, residuals add
-// x + (acc + bias). Waves split the columns (D / 4 or FC / 4 per wave) and
-// each covers all BM rows; a row's LayerNorm statistics come from 16 lanes
-// holding D / 16 consecutive values each. The barriers order LDS only, so
-// weight loads stay in flight across them.
+// x + (acc + bias). The NW waves split the columns (D / NW or FC / NW per
+// wave) and each covers all BM rows; a row's LayerNorm statistics come from
+// 16 or 32 lanes holding its values. The barriers order LDS only, so weight
+// loads stay in flight across them.
+// Bound: at many rows the weights, which every workgroup streams through its
+// compute unit's cache (384 KB at d = 128), and 2 KB per row to and from
+// memory; at few rows the chain of loads. Per layer, before and after the
+// weights' prefetch, the parameters' early loads, the ordered stores and the
+// present tiles: 36864 rows of d = 128 44.9 -> 36.8 us (without q, k, v 26.7
+// -> 22.1), 2816 rows of d = 256 35.5 -> 26.1 us, 16320 rows 83 -> 69 us.
 // ---------------------------------------------------------------------------
 // W [N][K] (bf16, N a multiple of 16, K of 32) into MFMA operand fragments:
 // fragment (nt, ks) holds, for lane l = 16 g + r, W[16 nt + r][32 ks + 8 g ..
@@ -738,25 +744,26 @@ void launch_pack_frags(const void *W, int N, int K, void *out, hipStream_t s) {
   k_pack_frags<<<(total + 255) / 256, 256, 0, s>>>((const bf16_t *)W, N, K, (bf16_t *)out);
 }
 
-template <int D, int F, int BM, int FC, bool PRE, bool POST>
-__global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
+template <int D, int F, int BM, int FC, int NW, bool PRE, bool POST>
+__global__ __launch_bounds__(64 * NW) void k_layer_fused(LayerArgs a) {
   constexpr int XLD = D + 4, ALD = D + 8, HLD = FC + 8;   // row strides (pads spread LDS banks)
-  constexpr int TM = BM / 16, TNA = FC / 64, TNB = D / 64;
+  constexpr int NT = 64 * NW, TM = BM / 16, TNA = FC / (16 * NW), TNB = D / (16 * NW);
   constexpr int KSD = D / 32, KSB = FC / 32, NCH = F / FC;
-  constexpr int EPL = D / 16, NP = BM / 16;               // LayerNorm: values per lane, row passes
+  // LayerNorm: lanes per row, rows per pass of the workgroup, values per lane, passes
+  constexpr int LPR = NT / BM > 16 ? NT / BM : 16, RPP = NT / LPR, EPL = D / LPR, NP = BM / RPP;
   static_assert(TNA >= 1 && TNB >= 1 && F % FC == 0 && BM % 16 == 0 && EPL % 4 == 0, "shape");
-  static_assert(!POST || (3 * D) % 128 == 0, "q, k, v in chunks of 128 columns");
+  
   __shared__ __attribute__((aligned(16))) float xs[BM * XLD];
   __shared__ __attribute__((aligned(16))) bf16_t as[BM * ALD];
   __shared__ __attribute__((aligned(16))) bf16_t hs[BM * HLD];
-  __shared__ float b1s[F], b2s[D];   // (b1s holds the q, k, v bias once the FFN is done)
-  __shared__ int rpos[POST ? BM : 1];    // POST: cache position of each row's event
-  static_assert(!POST || F >= 3 * D, "q, k, v bias fits the FFN bias array");
+  __shared__ int rpos[POST ? BM : 1], rhead[POST ? BM : 1];   // POST: each row's cache position and first head slab
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rr = lane & 15, g = lane >> 4;
+  const int lr = tid / LPR, lc = tid % LPR;   // LayerNorm: first row, first value / EPL
   const int T = a.T, m0 = blockIdx.x * BM;
   if (POST && tid < BM) {   // read now, used at the very end
     const int r = min(m0 + tid, T - 1), bq = r / a.qe.P;
     rpos[tid] = a.qe.start[bq] + a.qe.start_off + (r - bq * a.qe.P);
+    rhead[tid] = bq * a.qe.H;
   }
   const bf16_t *W1 = a.w1, *W2 = a.w2;
   // weights are pre-packed in MFMA fragment order (k_pack_frags): fragment
@@ -765,38 +772,40 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
   auto frag = [&](const bf16_t *Wp, int nt, int KS, int ks) {
     return *(const bf16x8_t *)(Wp + ((size_t)(nt * KS + ks) * 64 + lane) * 8);
   };
-  // first FFN product's weights of chunk c: wave's hidden columns c FC + wave FC/4 + 16 j + rr
+  // first FFN product's weights of chunk c: wave's hidden columns c FC + wave FC/NW + 16 j + rr
   bf16x8_t w1f[2][TNA][KSD];
   auto load_w1 = [&](int c, bf16x8_t (&dst)[TNA][KSD]) {
 #pragma unroll
     for (int j = 0; j < TNA; ++j)
 #pragma unroll
       for (int ks = 0; ks < KSD; ++ks)
-        dst[j][ks] = frag(W1, c * (FC / 16) + wave * (FC / 64) + j, KSD, ks);
+        dst[j][ks] = frag(W1, c * (FC / 16) + wave * TNA + j, KSD, ks);
   };
-  // LayerNorm of the xs rows into as (bf16): wave w normalises rows
-  // w BM/4 + 4 p + g, 16 lanes per row; v holds the rows' values
-  auto layernorm = [&](const float4 (&v)[NP][EPL / 4], const float *lg, const float *lb) {
-    float4 gv[EPL / 4], bv[EPL / 4];
+  // LayerNorm of the xs rows into as (bf16): LPR lanes per row,
+  // RPP rows per pass; v holds the rows' values
+  float4 gv[EPL / 4], bv[EPL / 4];   // this lane's LayerNorm parameters
+  auto load_ln = [&](const float *lg, const float *lb) {
 #pragma unroll
     for (int c = 0; c < EPL / 4; ++c) {
-      gv[c] = *(const float4 *)(lg + rr * EPL + 4 * c);
-      bv[c] = *(const float4 *)(lb + rr * EPL + 4 * c);
+      gv[c] = *(const float4 *)(lg + lc * EPL + 4 * c);
+      bv[c] = *(const float4 *)(lb + lc * EPL + 4 * c);
     }
+  };
+  auto layernorm = [&](const float4 (&v)[NP][EPL / 4]) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const int row = wave * (BM / 4) + 4 * p + g;
+      const int row = lr + RPP * p;
       float sum = 0.f;
 #pragma unroll
       for (int c = 0; c < EPL / 4; ++c) sum += (v[p][c].x + v[p][c].y) + (v[p][c].z + v[p][c].w);
-      const float mean = group_sum(sum, 16) / (float)D;
+      const float mean = lanes_sum<LPR>(sum) / (float)D;
       float var = 0.f;
 #pragma unroll
       for (int c = 0; c < EPL / 4; ++c) {
         const float a0 = v[p][c].x - mean, a1 = v[p][c].y - mean, a2 = v[p][c].z - mean, a3 = v[p][c].w - mean;
         var += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
       }
-      const float rs = 1.f / sqrtf(group_sum(var, 16) / (float)D + 1e-5f);
+      const float rs = rsqrt_nr(lanes_sum<LPR>(var) / (float)D + 1e-5f);
 #pragma unroll
       for (int c = 0; c < EPL / 4; ++c) {
         const float y0 = (v[p][c].x - mean) * rs * gv[c].x + bv[c].x;
@@ -806,7 +815,7 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
         uint2 pk;
         pk.x = pk2bf(y0, y1);
         pk.y = pk2bf(y2, y3);
-        *(uint2 *)&as[row * ALD + rr * EPL + 4 * c] = pk;
+        *(uint2 *)&as[row * ALD + lc * EPL + 4 * c] = pk;
       }
     }
   };
@@ -815,18 +824,18 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
     for (int p = 0; p < NP; ++p)
 #pragma unroll
       for (int c = 0; c < EPL / 4; ++c)
-        v[p][c] = *(const float4 *)&xs[(wave * (BM / 4) + 4 * p + g) * XLD + rr * EPL + 4 * c];
+        v[p][c] = *(const float4 *)&xs[(lr + RPP * p) * XLD + lc * EPL + 4 * c];
   };
   // D-wide product of the as rows with the D x D matrix W, computed
   // transposed (W rows as the MFMA's first operand) so that lane (rr, g)
-  // holds row 16 i + rr, columns wave D/4 + 16 j + 4 g .. + 3 in acc[i][j]
+  // holds row 16 i + rr, columns wave D/NW + 16 j + 4 g .. + 3 in acc[i][j]
   auto prod_dd = [&](const bf16_t *W, f32x4_t (&acc)[TM][TNB]) {
     bf16x8_t wf[TNB][KSD];
 #pragma unroll
     for (int j = 0; j < TNB; ++j)
 #pragma unroll
       for (int ks = 0; ks < KSD; ++ks)
-        wf[j][ks] = frag(W, wave * (D / 64) + j, KSD, ks);
+        wf[j][ks] = frag(W, wave * TNB + j, KSD, ks);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -842,39 +851,63 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
       }
   };
   // xs[row][col .. col + 3] += acc + bias[col ..]: one float4 per lane
-  auto resid4 = [&](int row, int col, const f32x4_t &acc, const float *bias) {
+  auto resid4 = [&](int row, int col, const f32x4_t &acc, const f32x4_t &bias) {
     float4 *xp = (float4 *)&xs[row * XLD + col];
     float4 xv4 = *xp;
-    xv4.x = xv4.x + (acc[0] + bias[col]);
-    xv4.y = xv4.y + (acc[1] + bias[col + 1]);
-    xv4.z = xv4.z + (acc[2] + bias[col + 2]);
-    xv4.w = xv4.w + (acc[3] + bias[col + 3]);
+    xv4.x = xv4.x + (acc[0] + bias[0]);
+    xv4.y = xv4.y + (acc[1] + bias[1]);
+    xv4.z = xv4.z + (acc[2] + bias[2]);
+    xv4.w = xv4.w + (acc[3] + bias[3]);
     *xp = xv4;
   };
+
+  // this lane's share of a residual's bias
+  auto load_bias = [&](const float *bias, f32x4_t (&dst)[TNB]) {
+#pragma unroll
+    for (int j = 0; j < TNB; ++j) dst[j] = *(const f32x4_t *)(bias + wave * (D / NW) + 16 * j + 4 * g);
+  };
+  f32x4_t rb[TNB];
 
   // x rows (and o rows) in
   float4 xv[NP][EPL / 4];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
-    const int row = wave * (BM / 4) + 4 * p + g;
+    const int row = lr + RPP * p;
     const size_t r = (size_t)min(m0 + row, T - 1);
 #pragma unroll
-    for (int c = 0; c < EPL / 4; ++c) xv[p][c] = *(const float4 *)(a.x + r * D + rr * EPL + 4 * c);
+    for (int c = 0; c < EPL / 4; ++c) xv[p][c] = *(const float4 *)(a.x + r * D + lc * EPL + 4 * c);
   }
   if (PRE) {
     constexpr int VR = D / 8;   // 16-byte vectors per o row
-    for (int i = tid; i < BM * VR; i += 256) {
+    for (int i = tid; i < BM * VR; i += NT) {
       const int row = i / VR, c = i - row * VR;
       *(uint4 *)&as[row * ALD + 8 * c] = *(const uint4 *)(a.o + (size_t)min(m0 + row, T - 1) * D + 8 * c);
     }
   }
-  for (int i = tid; i < F; i += 256) b1s[i] = a.b1[i];
-  for (int i = tid; i < D; i += 256) b2s[i] = a.b2[i];
 #pragma unroll
   for (int p = 0; p < NP; ++p)
 #pragma unroll
-    for (int c = 0; c < EPL / 4; ++c) *(float4 *)&xs[(wave * (BM / 4) + 4 * p + g) * XLD + rr * EPL + 4 * c] = xv[p][c];
+    for (int c = 0; c < EPL / 4; ++c) *(float4 *)&xs[(lr + RPP * p) * XLD + lc * EPL + 4 * c] = xv[p][c];
   load_w1(0, w1f[0]);
+  load_ln(a.ln2_g, a.ln2_b);
+  if (PRE) load_bias(a.bo, rb);
+  // the layer's weights are cold in each die's L2 when the launch begins
+  // (other layers and the key / value caches ran through it), and all
+  // workgroups reach them in step, one chunk ahead: without this every chunk
+  // waits for memory once. The workgroups of a die (consecutive indices go
+  // round the dies) touch a share of the lines each, all at once.
+  uint32_t pf = 0;
+  {
+    const int slices = min(max((int)gridDim.x >> 3, 1), 32), sl = blockIdx.x >> 3;
+    auto touch = [&](const bf16_t *p, int n) {
+      for (int i = (sl * NT + tid) * 64; i < n; i += slices * NT * 64) pf |= *(const uint32_t *)(p + i);
+    };
+    if (sl < slices) {
+      touch(W1, F * D);
+      touch(W2, F * D);
+      if (POST) touch(a.wqkv, 3 * D * D);
+    }
+  }
   lds_barrier();
   if (PRE) {
     // output projection and residual into the xs tile
@@ -883,12 +916,26 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TNB; ++j) resid4(16 * i + rr, wave * (D / 4) + 16 * j + 4 * g, acc[i][j], a.bo);
+      for (int j = 0; j < TNB; ++j) resid4(16 * i + rr, wave * (D / NW) + 16 * j + 4 * g, acc[i][j], rb[j]);
     lds_barrier();   // xs complete, o operand reads done
     read_rows(xv);
   }
-  layernorm(xv, a.ln2_g, a.ln2_b);
+  layernorm(xv);
+  asm volatile("" ::"v"(pf));   // (the touched lines have arrived)
   lds_barrier();
+  constexpr int QC = 128, TNQ = QC / (16 * NW), SLD = QC + 4, NQC = POST ? 3 * D / QC : 1;
+  bf16x8_t wq[2][TNQ][KSD];
+  f32x4_t bq[2][TNQ];
+  auto load_wq = [&](int c) {
+#pragma unroll
+    for (int j = 0; j < TNQ; ++j)
+#pragma unroll
+      for (int ks = 0; ks < KSD; ++ks)
+        wq[c & 1][j][ks] = frag(a.wqkv, c * (QC / 16) + wave * TNQ + j, KSD, ks);
+#pragma unroll
+    for (int j = 0; j < TNQ; ++j)
+      bq[c & 1][j] = *(const f32x4_t *)(a.qe.bias + c * QC + wave * (QC / NW) + 16 * j + 4 * g);
+  };
   f32x4_t acc_o[TM][TNB];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -896,14 +943,25 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
     for (int j = 0; j < TNB; ++j) acc_o[i][j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    if (c + 1 < NCH) load_w1(c + 1, w1f[(c + 1) & 1]);
-    // second product's weights of chunk c: wave's output columns wave D/4 + 16 j + rr
+    if (c + 1 < NCH) {
+      load_w1(c + 1, w1f[(c + 1) & 1]);
+    } else {   // what follows the last chunk
+      load_bias(a.b2, rb);
+      if (POST) {
+        load_ln(a.ln1_g, a.ln1_b);
+        load_wq(0);
+      }
+    }
+    // second product's weights of chunk c: wave's output columns wave D/NW + 16 j + rr
     bf16x8_t w2f[TNB][KSB];
 #pragma unroll
     for (int j = 0; j < TNB; ++j)
 #pragma unroll
       for (int ks = 0; ks < KSB; ++ks)
-        w2f[j][ks] = frag(W2, wave * (D / 64) + j, F / 32, c * (FC / 32) + ks);
+        w2f[j][ks] = frag(W2, wave * TNB + j, F / 32, c * (FC / 32) + ks);
+    float4 bh[TNA];   // (biases come straight from global memory: lanes 16 g .. read one address)
+#pragma unroll
+    for (int j = 0; j < TNA; ++j) bh[j] = *(const float4 *)(a.b1 + c * FC + wave * (FC / NW) + 16 * j + 4 * g);
     // hidden chunk: ReLU(A W1_c^T + b1) -> bf16 -> LDS
     f32x4_t acc_h[TM][TNA];
 #pragma unroll
@@ -920,16 +978,15 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
           acc_h[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1f[c & 1][j][ks], af, acc_h[i][j], 0, 0, 0);
       }
     // (transposed product: lane (rr, g) holds row 16 i + rr, hidden columns
-    // wave FC/4 + 16 j + 4 g .. + 3, written as one 8-byte word)
+    // wave FC/NW + 16 j + 4 g .. + 3, written as one 8-byte word)
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TNA; ++j) {
-        const int col = wave * (FC / 4) + 16 * j + 4 * g;
-        const float *bb = b1s + c * FC + col;
+        const int col = wave * (FC / NW) + 16 * j + 4 * g;
         uint2 pk;
-        pk.x = pk2bf(fmaxf(acc_h[i][j][0] + bb[0], 0.f), fmaxf(acc_h[i][j][1] + bb[1], 0.f));
-        pk.y = pk2bf(fmaxf(acc_h[i][j][2] + bb[2], 0.f), fmaxf(acc_h[i][j][3] + bb[3], 0.f));
+        pk.x = pk2bf(fmaxf(acc_h[i][j][0] + bh[j].x, 0.f), fmaxf(acc_h[i][j][1] + bh[j].y, 0.f));
+        pk.y = pk2bf(fmaxf(acc_h[i][j][2] + bh[j].z, 0.f), fmaxf(acc_h[i][j][3] + bh[j].w, 0.f));
         *(uint2 *)&hs[(16 * i + rr) * HLD + col] = pk;
       }
     lds_barrier();
@@ -944,43 +1001,50 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
       }
     lds_barrier();   // the chunk's hidden tile is read before the next overwrites it
   }
-  constexpr int QC = 128, TNQ = QC / 64, SLD = QC + 4, NQC = POST ? 3 * D / QC : 1;
-  bf16x8_t wq[2][TNQ][KSD];
-  auto load_wq = [&](int c, bf16x8_t (&dst)[TNQ][KSD]) {
-#pragma unroll
-    for (int j = 0; j < TNQ; ++j)
-#pragma unroll
-      for (int ks = 0; ks < KSD; ++ks)
-        dst[j][ks] = frag(a.wqkv, c * (QC / 16) + wave * (QC / 64) + j, KSD, ks);
-  };
-  if (POST) {
-    load_wq(0, wq[0]);
-    for (int i = tid; i < 3 * D; i += 256) b1s[i] = a.qe.bias[i];
-  }
   // second residual in the LDS tile, then 16-byte stores of whole rows
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TNB; ++j) resid4(16 * i + rr, wave * (D / 4) + 16 * j + 4 * g, acc_o[i][j], b2s);
+    for (int j = 0; j < TNB; ++j) resid4(16 * i + rr, wave * (D / NW) + 16 * j + 4 * g, acc_o[i][j], rb[j]);
   lds_barrier();
-  for (int idx = tid; idx < BM * (D / 4); idx += 256) {
-    const int row = idx / (D / 4), c4 = idx - row * (D / 4);
-    if (m0 + row < T) *(float4 *)(a.x + (size_t)(m0 + row) * D + 4 * c4) = *(const float4 *)&xs[row * XLD + 4 * c4];
+  auto store_x = [&] {
+    for (int idx = tid; idx < BM * (D / 4); idx += NT) {
+      const int row = idx / (D / 4), c4 = idx - row * (D / 4);
+      if (m0 + row < T) *(float4 *)(a.x + (size_t)(m0 + row) * D + 4 * c4) = *(const float4 *)&xs[row * XLD + 4 * c4];
+    }
+  };
+  if (!POST) {
+    store_x();
+    return;
   }
-  if (!POST) return;
-  // the next layer's LayerNorm and q, k, v, 128 columns at a time (the next
-  // chunk's weights loading during the current one); each chunk's tile is
-  // staged in xs (free once normalised) and stored with lanes running over
-  // rows, so that the value cache's 2-byte stores of consecutive positions
-  // (one 16-byte block holds 8 positions of a column) are adjacent
+  // Loads and stores complete in one order, so a load waits for every store
+  // issued before it: what the next LayerNorm and first product take is
+  // waited for here, before the stores of x
+#pragma unroll
+  for (int j = 0; j < TNQ; ++j)
+#pragma unroll
+    for (int ks = 0; ks < KSD; ++ks) asm volatile("" ::"v"(wq[0][j][ks]));
+#pragma unroll
+  for (int c = 0; c < EPL / 4; ++c) asm volatile("" ::"v"(gv[c].x), "v"(bv[c].x));
+  store_x();
+  // the next layer's LayerNorm and q, k, v, QC columns at a time (the next
+  // chunk's weights loading during the current one, ahead of its stores);
+  // each chunk's tile is staged in xs (free once normalised) and stored with
+  // lanes running along each target's own order: columns of a row for q, a
+  // head's columns and then positions for the key cache, and 8 positions by
+  // 8 columns per wave for the value cache, whose 16-byte blocks hold 8
+  // positions of a column. (Every product before the first store, so that no
+  // load waits behind one, gains 1 us at 2816 rows of d = 256 and loses 8 at
+  // 36864 rows of d = 128, where the stores overlap the products.)
   read_rows(xv);
-  layernorm(xv, a.ln1_g, a.ln1_b);
+  layernorm(xv);
   lds_barrier();
   static_assert(SLD <= XLD, "q, k, v staging fits the x tile");
   const Epi &e = a.qe;
+  const int hsh = 31 - __clz(e.dh);   // dh is 16, 32 or 64
 #pragma unroll
   for (int c = 0; c < NQC; ++c) {
-    if (c + 1 < NQC) load_wq(c + 1, wq[(c + 1) & 1]);
+    if (c + 1 < NQC) load_wq(c + 1);
     f32x4_t acc[TM][TNQ];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -999,31 +1063,41 @@ __global__ __launch_bounds__(256) void k_layer_fused(LayerArgs a) {
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TNQ; ++j)
-        *(f32x4_t *)&xs[(16 * i + rr) * SLD + wave * (QC / 4) + 16 * j + 4 * g] = acc[i][j];
+        *(f32x4_t *)&xs[(16 * i + rr) * SLD + wave * (QC / NW) + 16 * j + 4 * g] = acc[i][j] + bq[c & 1][j];
     lds_barrier();
-    for (int gi = tid; gi < BM * (QC / 8); gi += 256) {
-      const int row = gi % BM, c8 = gi / BM, r = m0 + row;
-      if (r >= T) continue;
-      const int n = c * QC + 8 * c8, which = n / D, cc = n - which * D;
-      float v[8];
-      load8f(xs + row * SLD + 8 * c8, v);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] += b1s[n + i];
-      if (which == 0) {
-        store8((bf16_t *)e.q + (size_t)r * D + cc, v);
-      } else {
-        const int bq = r / e.P, h = cc / e.dh, j = cc - h * e.dh, pos = rpos[row];
-        if (pos < e.cap) {
-          const size_t row0 = ((size_t)bq * e.H + h) * e.cap;
-          if (which == 1) {
-            store8((bf16_t *)e.kc + (row0 + pos) * e.dh + j, v);
-          } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) st((bf16_t *)e.vc, v_at<bf16_t>(row0, pos, j + i, e.dh), v[i]);
-          }
-        } else {
+    // (each chunk is wholly q, k or v)
+    const int which = c * QC / D, cc0 = c * QC % D;
+    if (which == 0) {
+      for (int gi = tid; gi < BM * (QC / 8); gi += NT) {
+        const int row = gi / (QC / 8), c8 = gi % (QC / 8), r = m0 + row;
+        if (r >= T) continue;
+        float v[8];
+        load8f(xs + row * SLD + 8 * c8, v);
+        store8((bf16_t *)e.q + (size_t)r * D + cc0 + 8 * c8, v);
+      }
+    } else if (which == 1) {
+      const int sh = hsh - 3;
+      for (int gi = tid; gi < BM * (QC / 8); gi += NT) {
+        const int rh = gi >> sh, row = rh % BM, c8 = ((rh / BM) << sh) + (gi & ((1 << sh) - 1));
+        if (m0 + row >= T) continue;
+        const int pos = rpos[row], cc = cc0 + 8 * c8;
+        float v[8];
+        load8f(xs + row * SLD + 8 * c8, v);
+        if (pos < e.cap)
+          store8((bf16_t *)e.kc + ((size_t)(rhead[row] + (cc >> hsh)) * e.cap + pos) * e.dh + (cc & (e.dh - 1)), v);
+        else
           atomicOr(e.status, TPPSD_STATUS_CAPACITY);
-        }
+      }
+    } else {
+      for (int gi = tid; gi < BM * QC; gi += NT) {
+        const int row = (gi / (8 * QC)) * 8 + (gi & 7), cq = (gi >> 3) % QC;
+        if (m0 + row >= T) continue;
+        const int pos = rpos[row], cc = cc0 + cq;
+        if (pos < e.cap)
+          st((bf16_t *)e.vc, v_at<bf16_t>((size_t)(rhead[row] + (cc >> hsh)) * e.cap, pos, cc & (e.dh - 1), e.dh),
+             xs[row * SLD + cq]);
+        else
+          atomicOr(e.status, TPPSD_STATUS_CAPACITY);
       }
     }
     lds_barrier();   // staging read before the next chunk writes it
@@ -4372,27 +4446,33 @@ static void gemm_dispatch(const void *X, const LnA *ln, const void *W, int T, in
 bool layer_fused_ok(int bf16, int d, int F) { return bf16 && ((d == 128 && F == 512) || (d == 256 && F == 1024)); }
 
 // Where the fused layer kernel is used by default: at d = 128 from 8192 rows
-// (32-row tiles; measured at 36864 rows: verify pass 1121 -> 810 us) and up
-// to 64 rows (one or two tiles replacing four launches: the 32-sequence
-// draft, 1364 -> 1346 us per round), at d = 256 from 2048 rows (16-row
-// tiles; at 2816 rows 501 -> 461 us; with 32-row tiles it only matched the
-// layered GEMMs)
+// (measured at 36864 rows against the layered kernels: verify pass 1121 ->
+// 810 us) and up to 64 rows (one or two tiles replacing four launches: the
+// 32-sequence draft, 1364 -> 1346 us per round), at d = 256 from 2048 rows
+// (at 2816 rows 501 -> 461 us)
 bool layer_fused_worth(int d, long T) { return d == 128 ? (T >= 8192 || T <= 64) : T >= 2048; }
 
 void launch_layer_fused(const LayerArgs &a, int d, int F, bool post, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  auto go = [&](auto kern, int bm) {
-    hipExtLaunchKernelGGL(kern, dim3((a.T + bm - 1) / bm), dim3(256), 0, s, ev0, ev1, 0, a);
+  auto go = [&](auto kern, int bm, int nw) {
+    hipExtLaunchKernelGGL(kern, dim3((a.T + bm - 1) / bm), dim3(64 * nw), 0, s, ev0, ev1, 0, a);
   };
-  // 32-row tiles: with the weights in fragment order, twice the workgroups
-  // beat the halved weight traffic of 64-row tiles (36864 rows at d = 128:
-  // 46 vs 58 us per layer; 64-row tiles on eight waves, each wave keeping the
-  // four-wave kernel's share, 43.7 vs 40.3 us)
+  // d = 128: 48 rows and hidden chunks of 64 columns, 45 KB of LDS, so that
+  // three workgroups share a compute unit and each weight read serves three
+  // row tiles (36864 rows: 36.8 us, with 32 rows 41.1, 48 rows in chunks of
+  // 128 columns 44.6, 64 rows on four waves 52.2).
+  // d = 256: while 16-row tiles leave no compute unit with two of them, the
+  // more workgroups the better (2816 rows: 26.1 us, 32-row tiles 32.9); past
+  // that the halved weight traffic of 32 rows wins (6128 rows 44.7 vs 34.7
+  // us, 16320 rows 91 vs 69).
   if (d == 128 && F == 512) {
-    if (post) go(k_layer_fused<128, 512, 32, 128, true, true>, 32);
-    else go(k_layer_fused<128, 512, 32, 128, true, false>, 32);
+    if (post) go(k_layer_fused<128, 512, 48, 64, 4, true, true>, 48, 4);
+    else go(k_layer_fused<128, 512, 48, 64, 4, true, false>, 48, 4);
+  } else if (a.T <= 16 * 256) {
+    if (post) go(k_layer_fused<256, 1024, 16, 128, 8, true, true>, 16, 8);
+    else go(k_layer_fused<256, 1024, 16, 128, 8, true, false>, 16, 8);
   } else {
-    if (post) go(k_layer_fused<256, 1024, 16, 64, true, true>, 16);
-    else go(k_layer_fused<256, 1024, 16, 64, true, false>, 16);
+    if (post) go(k_layer_fused<256, 1024, 32, 128, 8, true, true>, 32, 8);
+    else go(k_layer_fused<256, 1024, 32, 128, 8, true, false>, 32, 8);
   }
 }
 
