@@ -166,12 +166,14 @@ void tppsd_model_destroy(tppsd_model *m);
  * events each (history + generated + max_gamma + 1), draft length up to
  * max_gamma. It holds both KV caches ([layers][B][heads][max_events][d_head]
  * for keys and values), the committed events, per-sequence counters and
- * activation scratch. Errors: TPPSD_E_ARG. */
+ * activation scratch, which includes the rows of long prefill chunks.
+ * Errors: TPPSD_E_ARG. */
 int tppsd_state_bytes(const tppsd_model *target, const tppsd_model *draft, int B,
                       int max_events, int max_gamma, size_t *bytes);
 
 /* Creates a sampler state in the caller's workspace (256-byte aligned,
- * at least tppsd_state_bytes). `seed` keys the Philox4x64-10 streams of every
+ * tppsd_state_bytes or more; a workspace short of the prefill rows alone is
+ * also taken, and its prefill then runs in chunks of 16 positions). `seed` keys the Philox4x64-10 streams of every
  * draw; `flags` is a combination of TPPSD_FLAG_*. The draft model may be NULL
  * for an AR-only state. Copies a small constant table into the workspace
  * (synchronously). Errors: TPPSD_E_ARG, TPPSD_E_WORKSPACE, TPPSD_E_CONFIG,
@@ -259,9 +261,12 @@ int tppsd_sample_ar(tppsd_state *s, int n_events, float *d_t_out, int32_t *d_k_o
                     hipStream_t stream);
 
 /* Runs TPP-SD rounds (draft, verify, accept) with internal round buffers until
- * every sequence has its n_gen events or max_rounds rounds ran. Reads a done
- * counter back from the device once per round (one round behind). Returns the
- * number of rounds run in *rounds (may be NULL). Errors: as tppsd_draft. */
+ * every sequence has its n_gen events or max_rounds rounds ran. Without end
+ * times the rounds that the slowest sequence is certain to need are enqueued at
+ * once and its remaining events are read back after them; with end times, or
+ * with timing enabled, a done counter is read back once per round (one round
+ * behind). Returns the number of rounds run in *rounds (may be NULL). Errors:
+ * as tppsd_draft. */
 int tppsd_sample_sd(tppsd_state *s, int gamma, int max_rounds, int *rounds, hipStream_t stream);
 
 /* ---- homogeneous-Poisson draft (App. D.3) ------------------------------------
