@@ -72,6 +72,15 @@ size_t prefill_rows(int B, int cap) {
   return (size_t)B * std::min<size_t>(want, std::max(cap, PREFILL_CHUNK));
 }
 
+// Verify attention of caches of 512 MiB and more over all layers reads keys
+// and values with the non-temporal hint: nothing of them is left in the 256 MB
+// last-level cache by the next pass, and passing by they push out weights and
+// rows (per pass: 970 MB of d = 256 395 -> 366 us, 1.4 GB of d = 512 550 ->
+// 517, 397 MB of capacity at d = 128 225 -> 223). Smaller caches are found
+// there again (402 MB of capacity 294 -> 298 us, 332 MB 264 -> 282, 201 MB 173
+// -> 187). Returns launch_attention's verify argument.
+int verify_role(int L, size_t layer_bytes) { return 2 * (size_t)L * layer_bytes >= (size_t)512 << 20 ? 2 : 1; }
+
 // ---- packed weight layout -------------------------------------------------
 struct Entry {
   std::string name;
@@ -461,7 +470,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
       launch_gemm(s->u, nullptr, w.qkv_w, bf, T, 3 * d, 2 * d, e, st, ev(L + 4 * l, 0), ev(L + 4 * l, 1));
       if (!head && l + 1 == L) break;   // (prefill: past the last layer's keys and values nothing is used)
       launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                       1, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
+                       1, verify ? verify_role(L, c.layer_bytes) : 0, ev(l, 0), ev(l, 1), st);
       launch_attnhp_update(s->x, s->o, s->u, s->a, bf, T, d, st);
     }
   }
@@ -523,7 +532,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
       const bool last = l + 1 == L;
       if (last && !head) break;
       launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                       0, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
+                       0, verify ? verify_role(L, c.layer_bytes) : 0, ev(l, 0), ev(l, 1), st);
       const LayerW &w = m->layers[l];
       ba.first = 0;
       ba.pre = 1;
@@ -584,7 +593,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     }
     if (!head && l + 1 == L) break;   // (prefill: past the last layer's keys and values nothing is used)
     launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                     0, verify ? 1 : 0, ev(l, 0), ev(l, 1), st);
+                     0, verify ? verify_role(L, c.layer_bytes) : 0, ev(l, 0), ev(l, 1), st);
     if (use_layer_fused) {
       LayerArgs la{};
       la.x = s->x;

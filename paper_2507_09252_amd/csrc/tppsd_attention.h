@@ -33,7 +33,8 @@ inline size_t attn_part_floats(int B, int H, int dh, int qtiles_max, int max_key
 // many new positions per sequence; longer blocks (prefill chunks) run
 // k_attn_rows, which splits the queries instead of the keys and has no partials.
 constexpr int ATTN_ROWS_MIN_P = 16;
-// sink: AttNHP normalisation 1 + sum f (an extra key of score 0, value 0)
+// sink: AttNHP normalisation 1 + sum f (an extra key of score 0, value 0);
+// verify: 1 = the verify pass, 2 = with non-temporal cache loads (bf16), 0 = other
 void launch_attention(const void *q, const void *kc, const void *vc, void *o, int bf16,
                       const int32_t *start, int start_off, const int32_t *done, int B, int P, int H,
                       int dh, int cap, float *part, int sink, int verify, hipEvent_t ev0, hipEvent_t ev1,

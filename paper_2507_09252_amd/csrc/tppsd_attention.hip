@@ -18,7 +18,8 @@ namespace tppsd {
 // 0 .. start[b] + start_off + p. Online softmax over 64-key tiles.
 // ---------------------------------------------------------------------------
 
-// ROLE tags the instantiation only (1 = verify pass of the target, 0 = other
+// ROLE: 1 = verify pass of the target, 2 = the same with non-temporal loads of
+// keys and values (bf16; caches too large to stay on the chip), 0 = other
 // passes), so that profiles report the verify launches under their own name.
 // AttNHP attention (App. D.4) divides by 1 + sum f instead of sum f: the same
 // as one more key of score 0 and value 0. Applied once, where the softmax
@@ -46,6 +47,10 @@ __device__ __forceinline__ void sink_adjust(float &M, float &L, float &O) {
 // (l mod 16) for the 8 consecutive keys 8 (l / 16) .. + 7: exactly the B
 // operand of O^T = V^T P^T. The A operand (8 consecutive keys of one value
 // column) is one 16-byte load from the position-blocked value cache.
+
+template <bool NT> __device__ __forceinline__ bf16x8_t ld_kv(const bf16x8_t *p) {
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
 
 // The narrow one-tile kernel is held to 64 registers, so that eight waves and
 // not seven share a SIMD (2040 workgroups over 511 keys: 36 -> 34.9 us).
@@ -120,8 +125,8 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
     if (DH >= 32) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        a0[c] = *(const bf16x8_t *)(kc + r0 * DH + 32 * c + 8 * g);
-        a1[c] = *(const bf16x8_t *)(kc + r1 * DH + 32 * c + 8 * g);
+        a0[c] = ld_kv<ROLE == 2>((const bf16x8_t *)(kc + r0 * DH + 32 * c + 8 * g));
+        a1[c] = ld_kv<ROLE == 2>((const bf16x8_t *)(kc + r1 * DH + 32 * c + 8 * g));
       }
     } else {
       b0 = *(const short4_t *)(kc + r0 * DH + 4 * g);
@@ -137,7 +142,8 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
     uint4 vw[NDT];
 #pragma unroll
     for (int td = 0; td < NDT; ++td)
-      vw[td] = *(const uint4 *)(vc + kvbase * DH + (size_t)(k8c >> 3) * (8 * DH) + (16 * td + rr) * 8);
+      vw[td] = __builtin_bit_cast(uint4, ld_kv<ROLE == 2>((const bf16x8_t *)(vc + kvbase * DH + (size_t)(k8c >> 3) * (8 * DH) +
+                                                                       (16 * td + rr) * 8)));
     if (!interior && nv < 8) {
 #pragma unroll
       for (int td = 0; td < NDT; ++td) {
@@ -839,15 +845,17 @@ template <int ROLE>
 static void attention_role(const void *q, const void *kc, const void *vc, void *o, int bf16, const int32_t *start,
                            int start_off, const int32_t *done, int B, int P, int H, int dh, int cap, float *part,
                            int sink, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
-  if (!bf16) {
-    const float *Q = (const float *)q, *Kc = (const float *)kc, *Vc = (const float *)vc;
-    float *O = (float *)o;
-    switch (dh) {
-      case 16: attn_mfma<float, 16, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-      case 32: attn_mfma<float, 32, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-      default: attn_mfma<float, 64, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
+  if constexpr (ROLE != 2) {
+    if (!bf16) {
+      const float *Q = (const float *)q, *Kc = (const float *)kc, *Vc = (const float *)vc;
+      float *O = (float *)o;
+      switch (dh) {
+        case 16: attn_mfma<float, 16, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
+        case 32: attn_mfma<float, 32, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
+        default: attn_mfma<float, 64, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
+      }
+      return;
     }
-    return;
   }
   const bf16_t *Q = (const bf16_t *)q, *Kc = (const bf16_t *)kc, *Vc = (const bf16_t *)vc;
   bf16_t *O = (bf16_t *)o;
@@ -861,7 +869,9 @@ static void attention_role(const void *q, const void *kc, const void *vc, void *
 void launch_attention(const void *q, const void *kc, const void *vc, void *o, int bf16, const int32_t *start,
                       int start_off, const int32_t *done, int B, int P, int H, int dh, int cap, float *part,
                       int sink, int verify, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
-  if (verify)
+  if (verify == 2 && bf16)
+    attention_role<2>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, ev0, ev1, s);
+  else if (verify)
     attention_role<1>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, ev0, ev1, s);
   else
     attention_role<0>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, ev0, ev1, s);
