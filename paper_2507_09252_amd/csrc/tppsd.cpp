@@ -578,6 +578,15 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     e.status = s->status;
     return e;
   };
+  // a LayerNorm of its own sums a history position's row as a pass over
+  // PREFILL_CHUNK positions would (in the product's order where that has less
+  // rows than gemm_ln_split takes): the bits do not depend on the chunk
+  int ln_tile_from = P;
+  if (!head && fuse_ln) {
+    const int rest = P % PREFILL_CHUNK;
+    if (!gemm_ln_split(bf, d, B * PREFILL_CHUNK)) ln_tile_from = 0;
+    else if (rest && !gemm_ln_split(bf, d, B * rest)) ln_tile_from = P - rest;
+  }
   if (!m->attnhp()) launch_embed(s->x, T, d, P, src, m->type_emb, bf, c.freq, m->cfg.n_types, st);
   // LayerNorm inside the consuming GEMM, or (wide rows, many rows) as its own launch
   const bool ln_gemm = fuse_ln && !gemm_ln_split(bf, d, T);
@@ -586,7 +595,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     char *kc = c.k + c.layer_bytes * l, *vc = c.v + c.layer_bytes * l;
     const LnA ln1{s->x, w.ln1_g, w.ln1_b}, ln2{s->x, w.ln2_g, w.ln2_b};
     if (!(use_layer_fused && l > 0)) {   // (else the previous fused launch wrote this layer's q, k, v)
-      if (!ln_gemm) launch_layernorm(s->x, s->a, bf, w.ln1_g, w.ln1_b, T, d, st);
+      if (!ln_gemm) launch_layernorm(s->x, s->a, bf, w.ln1_g, w.ln1_b, T, d, P, ln_tile_from, st);
       const Epi e = qkv_epi(l);
       launch_gemm(s->a, ln_gemm ? &ln1 : nullptr, w.qkv_w, bf, T, 3 * d, d, e, st, ev(L + 4 * l, 0),
                   ev(L + 4 * l, 1));
@@ -625,7 +634,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     eo.out = s->x;
     eo.ldo = d;
     launch_gemm(s->o, nullptr, w.out_w, bf, T, d, d, eo, st, ev(L + 4 * l + 1, 0), ev(L + 4 * l + 1, 1));
-    if (!ln_gemm) launch_layernorm(s->x, s->a, bf, w.ln2_g, w.ln2_b, T, d, st);
+    if (!ln_gemm) launch_layernorm(s->x, s->a, bf, w.ln2_g, w.ln2_b, T, d, P, ln_tile_from, st);
     Epi e1{};
     e1.mode = EPI_RELU;
     e1.bias = w.ffn1_b;
@@ -643,7 +652,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     // THP: the decoder reads LN_f(x); AttNHP: h itself (a, written by the update)
     const LnA lnf{s->x, m->lnf_g, m->lnf_b};
     const bool ln_in_gemm = fuse_ln && !m->attnhp() && !gemm_ln_split(bf, d, T);
-    if (!ln_in_gemm && !m->attnhp()) launch_layernorm(s->x, s->a, bf, m->lnf_g, m->lnf_b, T, d, st);
+    if (!ln_in_gemm && !m->attnhp()) launch_layernorm(s->x, s->a, bf, m->lnf_g, m->lnf_b, T, d, P, P, st);
     Epi eh{};
     eh.mode = EPI_HEAD;
     eh.bias = m->k1_b;

@@ -181,18 +181,17 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
         const int key = kt + 8 * g + j;
         const float raw = (j < 4) ? s0[j] : s1[j - 4];
         const bool ok = interior || (q_ok && key < k_end && key <= my_last);
-        sv[j] = ok ? raw : -INFINITY;
+        sv[j] = ok ? raw * scale2 : -INFINITY;
         mx = fmaxf(mx, sv[j]);
       }
-      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)) * scale2);
+      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)));
       // (exp2 of -inf is 0: masked keys and an empty running state drop out)
       const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
       const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
       uint32_t pw[4];
 #pragma unroll
       for (int j = 0; j < 8; j += 2)
-        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(fmaf(sv[j], scale2, -m_ref)),
-                           __builtin_amdgcn_exp2f(fmaf(sv[j + 1], scale2, -m_ref)));
+        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
       // P V takes the probabilities in bf16; the normaliser (the ones rows)
       // sums the same rounded values, so the output stays a convex
       // combination of values
@@ -473,35 +472,39 @@ __global__ __launch_bounds__(256) void k_attn_mfma_f32(int H, int P, const int32
 }
 
 // ---------------------------------------------------------------------------
-// Causal attention of a long block of new queries (prefill chunks): a wave
-// owns 16 QT consecutive queries of one (sequence, head) and walks every key
-// up to its last query by itself, 32 keys per step, so that nothing is merged
-// and no barrier is taken. Same products, operand layouts, rounding points
-// and masks as the split-key kernels above.
+// Causal attention of a long block of new queries (prefill chunks): a
+// workgroup owns 16 QT consecutive queries of one (sequence, head); its four
+// waves take the 32-key steps round robin and are merged in LDS, operation for
+// operation as k_attn_mfma does with one split. A query's result then depends
+// neither on the length of the block it is encoded in nor on the others in it:
+// in 16 bits another order of these sums changes roundings, and with them every
+// event that is sampled later.
 // What bounds it: the loads of keys and values (8 KB a step at d_head 64)
-// through the L1, about 130 cycles a step against the 18 matrix products and
-// the softmax of 32 queries; they come from L2, where a (sequence, head) slab
-// of a seed history fits, so the next step's are issued before the current
-// step is computed. Two query tiles per wave halve the key traffic of one;
-// the grid puts the block's last (longest) queries first. Measured at 32
-// sequences x 8 heads x 511 queries of d_head 64: 36 us, against 32 launches
-// of k_attn_mfma over 16 queries each, 7.3 us on average.
+// through the L1 and their latency; they come from L2, where a (sequence, head)
+// slab of a seed history fits. A wave has a step or two at these lengths, so
+// waves per SIMD count and not loads ahead: 32 queries and 128 registers.
+// Measured at 32 sequences x 8 heads x 511 queries of d_head 64: 38 us (with the
+// next step loaded ahead 54, in 168 registers 46; 16 queries 55, 64 queries 43;
+// a wave over all keys of its 32 queries, nothing to merge, 36), against 32
+// launches of k_attn_mfma over 16 queries each, 7.3 us on average. The grid
+// puts the block's last (longest) queries first.
 // ---------------------------------------------------------------------------
 template <int DH, int QT>
-__global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *__restrict__ start,
+__global__ __launch_bounds__(256, 4) void k_attn_rows(int H, int P, const int32_t *__restrict__ start,
                                                    const int32_t *__restrict__ done, int start_off,
                                                    const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc,
                                                    const bf16_t *__restrict__ vc, bf16_t *__restrict__ o, int cap,
                                                    int sink) {
-  constexpr int KT = 32, NDT = DH / 16, NC = DH >= 32 ? DH / 32 : 1;
+  constexpr int KT = 32, NDT = DH / 16, NC = DH >= 32 ? DH / 32 : 1, NW = 4;
+  __shared__ float red_m[NW][16 * QT], red_l[NW][16 * QT];
+  __shared__ f32x4_t red_o[NW][QT * NDT][64];
   const int bh = blockIdx.x, b = bh / H, h = bh - b * H;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, rr = lane & 15, g = lane >> 4;
   const int d = H * DH;
-  const int q0 = ((gridDim.y - 1 - blockIdx.y) * 4 + wave) * 16 * QT;
-  if (q0 >= P) return;
+  const int q0 = (gridDim.y - 1 - blockIdx.y) * 16 * QT;
   const int base = start[b] + start_off;
   const bool skip = done != nullptr && done[b] != 0;
-  const int k_end = skip ? 0 : min(base + min(q0 + 16 * QT, P), cap);   // keys of the wave's last query, within the slab
+  const int k_end = skip ? 0 : min(base + min(q0 + 16 * QT, P), cap);   // keys of the last query, within the slab
   const size_t kvbase = ((size_t)b * H + h) * cap;
   const float scale2 = 1.4426950408889634f / sqrtf((float)DH);   // base-2 scores, as above
   constexpr float LN2 = 0.69314718055994531f;
@@ -509,7 +512,7 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
   bf16x8_t qf[QT][NC];
   short4_t qf16[QT];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
+  for (int t = 0; t < QT; ++t) {   // (queries past P repeat the last; they are not stored)
     const bf16_t *qp = q + (size_t)(b * P + min(q0 + 16 * t + rr, P - 1)) * d + h * DH;
     if (DH >= 32) {
 #pragma unroll
@@ -528,48 +531,41 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
     for (int td = 0; td < NDT; ++td) oacc[t][td] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
   }
   const int krow0 = 8 * (rr >> 2) + (rr & 3), krow1 = krow0 + 4;
-  struct Step {
+  for (int kt = KT * wave; kt < k_end; kt += NW * KT) {
+    // (unconditional: rows past the slab and value blocks past the key range
+    // are clamped into them and masked below)
     bf16x8_t a0[NC], a1[NC];
     short4_t b0, b1;
     uint4 vw[NDT];
-  };
-  // (unconditional: rows past the slab and value blocks past the key range
-  // are clamped into them and masked below)
-  auto fetch = [&](Step &f, int kt) {
     const bf16_t *kp = kc + (kvbase + kt) * DH, *vp = vc + (kvbase + kt) * DH;   // (uniform)
     const int left = cap - 1 - kt;
     const int r0 = min(krow0, left) * DH, r1 = min(krow1, left) * DH;
     if (DH >= 32) {
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        f.a0[c] = *(const bf16x8_t *)(kp + (r0 + 32 * c + 8 * g));
-        f.a1[c] = *(const bf16x8_t *)(kp + (r1 + 32 * c + 8 * g));
+        a0[c] = *(const bf16x8_t *)(kp + (r0 + 32 * c + 8 * g));
+        a1[c] = *(const bf16x8_t *)(kp + (r1 + 32 * c + 8 * g));
       }
     } else {
-      f.b0 = *(const short4_t *)(kp + (r0 + 4 * g));
-      f.b1 = *(const short4_t *)(kp + (r1 + 4 * g));
+      b0 = *(const short4_t *)(kp + (r0 + 4 * g));
+      b1 = *(const short4_t *)(kp + (r1 + 4 * g));
     }
     const int v0 = min(g, ((k_end - 1) >> 3) - (kt >> 3)) * (8 * DH) + rr * 8;
 #pragma unroll
-    for (int td = 0; td < NDT; ++td) f.vw[td] = *(const uint4 *)(vp + (v0 + 128 * td));
-  };
-  Step cur, nxt;
-  if (k_end > 0) fetch(cur, 0);
-  for (int kt = 0; kt < k_end; kt += KT) {
-    fetch(nxt, min(kt + KT, (k_end - 1) & ~(KT - 1)));   // (the last step's again past the end, unused)
+    for (int td = 0; td < NDT; ++td) vw[td] = *(const uint4 *)(vp + (v0 + 128 * td));
     const bool interior = kt + KT <= base + q0 + 1 && kt + KT <= k_end;   // every key visible to every query
     if (!interior) {
       const int nv = k_end - (kt + 8 * g);
       if (nv < 8) {
 #pragma unroll
         for (int td = 0; td < NDT; ++td) {
-          uint32_t w[4] = {cur.vw[td].x, cur.vw[td].y, cur.vw[td].z, cur.vw[td].w};
+          uint32_t w[4] = {vw[td].x, vw[td].y, vw[td].z, vw[td].w};
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             if (2 * i >= nv) w[i] = 0u;
             else if (2 * i + 1 >= nv) w[i] &= 0xFFFFu;
           }
-          cur.vw[td] = (uint4){w[0], w[1], w[2], w[3]};
+          vw[td] = (uint4){w[0], w[1], w[2], w[3]};
         }
       }
     }
@@ -579,12 +575,12 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
       if (DH >= 32) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a0[c], qf[t][c], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a1[c], qf[t][c], s1, 0, 0, 0);
+          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[c], qf[t][c], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[c], qf[t][c], s1, 0, 0, 0);
         }
       } else {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur.b0, qf16[t], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur.b1, qf16[t], s1, 0, 0, 0);
+        s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b0, qf16[t], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b1, qf16[t], s1, 0, 0, 0);
       }
       const int my_last = base + q0 + 16 * t + rr;
       float sv[8];
@@ -594,17 +590,16 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
         const int key = kt + 8 * g + j;
         const float raw = (j < 4) ? s0[j] : s1[j - 4];
         const bool ok = interior || (key < k_end && key <= my_last);
-        sv[j] = ok ? raw : -INFINITY;
+        sv[j] = ok ? raw * scale2 : -INFINITY;
         mx = fmaxf(mx, sv[j]);
       }
-      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)) * scale2);
+      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)));
       const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
       const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
       uint32_t pw[4];
 #pragma unroll
       for (int j = 0; j < 8; j += 2)
-        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(fmaf(sv[j], scale2, -m_ref)),
-                           __builtin_amdgcn_exp2f(fmaf(sv[j + 1], scale2, -m_ref)));
+        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
       const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, (uint4){pw[0], pw[1], pw[2], pw[3]});
       m_run[t] = m_new;
       if (__ballot(alpha != 1.f) != 0ull) {
@@ -615,27 +610,47 @@ __global__ __launch_bounds__(256) void k_attn_rows(int H, int P, const int32_t *
       lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, lacc[t], 0, 0, 0);
 #pragma unroll
       for (int td = 0; td < NDT; ++td)
-        oacc[t][td] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, cur.vw[td]), pb,
+        oacc[t][td] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vw[td]), pb,
                                                               oacc[t][td], 0, 0, 0);
     }
-    cur = nxt;
   }
   // lane (rr, g) holds O^T[16 td + 4 g + i][query 16 t + rr]: four consecutive columns
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
-    const int qq = q0 + 16 * t + rr;
-    if (qq >= P) continue;
-    float L = lacc[t][0], f = 1.f;
-    if (sink) {
-      const float M = m_run[t] * LN2, ms = fmaxf(M, 0.f);
-      f = (M == -INFINITY) ? 0.f : expf(M - ms);
-      L = L * f + expf(-ms);
+    if (g == 0) {
+      red_m[wave][16 * t + rr] = m_run[t];
+      red_l[wave][16 * t + rr] = lacc[t][0];
     }
-    const float r = L > 0.f ? f / L : 0.f;
 #pragma unroll
-    for (int td = 0; td < NDT; ++td)
-      *(uint2 *)(o + (size_t)(b * P + qq) * d + h * DH + 16 * td + 4 * g) =
-          make_uint2(pk2bf(oacc[t][td][0] * r, oacc[t][td][1] * r), pk2bf(oacc[t][td][2] * r, oacc[t][td][3] * r));
+    for (int td = 0; td < NDT; ++td) red_o[wave][t * NDT + td][lane] = oacc[t][td];
+  }
+  __syncthreads();
+  for (int f = wave; f < QT * NDT; f += NW) {   // (uniform)
+    const int t = f / NDT, td = f % NDT, qq = q0 + 16 * t + rr;
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, red_m[w][16 * t + rr]);
+    float L = 0.f, O[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float mw = red_m[w][16 * t + rr];
+      const float e = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+      L += red_l[w][16 * t + rr] * e;
+      const f32x4_t ow = red_o[w][f][lane];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) O[i] += ow[i] * e;
+    }
+    M *= LN2;   // natural units from here
+    if (sink) {
+      const float ms = fmaxf(M, 0.f), fs = (M == -INFINITY) ? 0.f : expf(M - ms);
+      L = L * fs + expf(-ms);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) O[i] *= fs;
+    }
+    if (qq >= P) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) O[i] = L > 0.f ? O[i] / L : 0.f;
+    *(uint2 *)(o + (size_t)(b * P + qq) * d + h * DH + 16 * td + 4 * g) = make_uint2(pk2bf(O[0], O[1]), pk2bf(O[2], O[3]));
   }
 }
 
@@ -793,17 +808,16 @@ static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const 
                       const int32_t *done, int B, int P, int H, int cap, float *part, int sink, hipEvent_t ev0,
                       hipEvent_t ev1, hipStream_t s) {
   if (ROLE == 0 && P > ATTN_ROWS_MIN_P) {
-    // a prefill chunk: waves of 32 queries (16 while that leaves compute units idle)
+    // a prefill chunk
     auto rows = [&](auto kern, int per_wg) {
       hipExtLaunchKernelGGL(kern, dim3(B * H, (P + per_wg - 1) / per_wg), dim3(256), 0, s, ev0, ev1, 0, H, P, start,
                             done, start_off, Q, Kc, Vc, O, cap, sink);
     };
-    const bool two = (long)B * H * ((P + 127) / 128) >= 256;
     if constexpr (sizeof(ACT) == 2) {
-      if (two) rows(k_attn_rows<DH, 2>, 128);
-      else rows(k_attn_rows<DH, 1>, 64);
+      rows(k_attn_rows<DH, 2>, 32);
     } else {
-      if (two) rows(k_attn_rows_f32<DH, 2>, 128);
+      // waves of 32 queries (16 while that leaves compute units idle)
+      if ((long)B * H * ((P + 127) / 128) >= 256) rows(k_attn_rows_f32<DH, 2>, 128);
       else rows(k_attn_rows_f32<DH, 1>, 64);
     }
     return;

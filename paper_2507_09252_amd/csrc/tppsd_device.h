@@ -95,8 +95,8 @@ __device__ __forceinline__ float xor32_sum(float v) {
 __device__ __forceinline__ float group_sum(float v, int width) {
   if (width >= 2) v += dpp_mov<0xB1>(v);   // quad_perm(1, 0, 3, 2): lane ^ 1
   if (width >= 4) v += dpp_mov<0x4E>(v);   // quad_perm(2, 3, 0, 1): lane ^ 2
-  if (width >= 8) v += swz_xor<4>(v);
-  if (width >= 16) v += swz_xor<8>(v);
+  if (width >= 8) v += dpp_mov<0x141>(v);    // row_half_mirror: quad ^ 1 (a quad's lanes are equal by now)
+  if (width >= 16) v += dpp_mov<0x140>(v);   // row_mirror: eight ^ 1
   if (width >= 32) v += swz_xor<16>(v);
   if (width >= 64) v += __shfl_xor(v, 32, 64);
   return v;

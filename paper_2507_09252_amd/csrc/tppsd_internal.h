@@ -289,8 +289,10 @@ void launch_draft_fused(const DraftArgs &a, int bf16, hipStream_t st, hipEvent_t
 int allow_draft_fused_lds(size_t bytes);
 void launch_embed(float *x, int T, int d, int P, const TokSrc &src, const void *wtype, int bf16,
                   const float *freq, int K, hipStream_t st);
-void launch_layernorm(const float *x, void *y, int bf16, const float *g, const float *b, int T, int d,
-                      hipStream_t st);
+// P positions per sequence; those from tile_from on (P: none) are summed in the order of
+// the products that normalise their own operand (d a multiple of 256)
+void launch_layernorm(const float *x, void *y, int bf16, const float *g, const float *b, int T, int d, int P,
+                      int tile_from, hipStream_t st);
 // AttNHP: h^(0) = W_type[k] into x (fp32) and u = [z(t); h] (activation type, [T, 2d])
 void launch_embed_attnhp(float *x, void *u, int T, int d, int P, const TokSrc &src, const void *wtype, int bf16,
                          const float *freq, int K, hipStream_t st);

@@ -187,11 +187,35 @@ __device__ __forceinline__ void st4(bf16_t *p, size_t i, float a, float b, float
 template <typename ACT>
 __global__ __launch_bounds__(256) void k_layernorm(const float *__restrict__ x, ACT *__restrict__ y,
                                                    const float *__restrict__ g, const float *__restrict__ bt,
-                                                   int T, int d) {
+                                                   int T, int d, int P, int tile_from) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (row >= T) return;
   const float *xr = x + (size_t)row * d;
+  // a row's sum from each lane's parts: over the lanes, or (positions from
+  // tile_from on, of P per sequence; widths of 256 and more) in the order of
+  // the products that normalise their own operand: over vectors of 8 columns,
+  // 128 columns apart, then over the 16 vectors of 128 columns
+  const bool tiled = row % P >= tile_from;   // (one row per wave)
+  auto row_sum = [&](const float (&part)[LN_VEC_MAX]) {
+    float s = 0.f;
+    if (!tiled) {
+#pragma unroll
+      for (int i = 0; i < LN_VEC_MAX; ++i)
+        if (4 * (lane + 64 * i) < d) s += part[i];
+      return wave_sum(s);
+    }
+#pragma unroll
+    for (int i = 0; i < LN_VEC_MAX; ++i) {
+      if (256 * i >= d) break;   // (uniform)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s += __shfl(part[i], 32 * (c >> 1) + (lane & 30) + (c & 1), 64);
+    }
+    s += swz_xor<2>(s);
+    s += swz_xor<4>(s);
+    s += swz_xor<8>(s);
+    return s + swz_xor<16>(s);
+  };
   const bool vec = d % 4 == 0 && d <= 4 * 64 * LN_VEC_MAX &&
                    (((uintptr_t)x | (uintptr_t)g | (uintptr_t)bt) & 15) == 0 && ((uintptr_t)y & 7) == 0;
   if (vec) {
@@ -205,19 +229,16 @@ __global__ __launch_bounds__(256) void k_layernorm(const float *__restrict__ x, 
       gv[i] = *(const float4 *)(g + jc);
       bv[i] = *(const float4 *)(bt + jc);
     }
-    float s = 0.f;
+    float part[LN_VEC_MAX];
 #pragma unroll
-    for (int i = 0; i < LN_VEC_MAX; ++i)
-      if (4 * (lane + 64 * i) < d) s += (xv[i].x + xv[i].y) + (xv[i].z + xv[i].w);
-    const float mean = wave_sum(s) / (float)d;
-    float v = 0.f;
+    for (int i = 0; i < LN_VEC_MAX; ++i) part[i] = (xv[i].x + xv[i].y) + (xv[i].z + xv[i].w);
+    const float mean = row_sum(part) / (float)d;
 #pragma unroll
-    for (int i = 0; i < LN_VEC_MAX; ++i)
-      if (4 * (lane + 64 * i) < d) {
-        const float c0 = xv[i].x - mean, c1 = xv[i].y - mean, c2 = xv[i].z - mean, c3 = xv[i].w - mean;
-        v += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
-      }
-    const float rstd = 1.f / sqrtf(wave_sum(v) / (float)d + 1e-5f);
+    for (int i = 0; i < LN_VEC_MAX; ++i) {
+      const float c0 = xv[i].x - mean, c1 = xv[i].y - mean, c2 = xv[i].z - mean, c3 = xv[i].w - mean;
+      part[i] = (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
+    }
+    const float rstd = 1.f / sqrtf(row_sum(part) / (float)d + 1e-5f);
 #pragma unroll
     for (int i = 0; i < LN_VEC_MAX; ++i) {
       const int j = 4 * (lane + 64 * i);
@@ -1268,20 +1289,26 @@ __global__ __launch_bounds__(256) void k_gemm_dl(const bf16_t *__restrict__ X, c
 
 // ---------------------------------------------------------------------------
 // GEMM for few rows (AR steps, per-step drafting, small verify passes): a
-// workgroup owns 16 rows x 16 columns and its NW waves split K, NS MFMA
-// k-steps each (K = NW NS KSTEP), so that a product is one batch of loads
-// straight into operand registers, NS matrix instructions, one exchange of
-// the waves' partial sums through LDS and the epilogue.
+// workgroup owns 16 rows x 16 columns and its NW waves split the operands' K,
+// NS MFMA k-steps each (K = NW NS KSTEP), so that a product is one batch of
+// loads straight into LDS.
 // What bounds it: latency. The products of a 32-row pass move a few hundred
 // KB; a tile walked stage by stage through LDS pays a barrier and an LDS
 // round trip per stage, and 32 x 32 tiles leave most CUs idle (N = 512: 16
-// workgroups). The order of the waves' sums is fixed. Measured at 32 rows
-// against the tile walked in stages: N = 512, K = 512 4.4 us and K = 2048 3.7
-// (6.8 on average); with a LayerNorm operand, K = 512, N = 1536 4.6 vs 8.0 and
-// N = 2048 4.2 vs 7.8; the decoder heads (53 columns, K = 2048) 3.1 vs 9.6.
-// LN: the A operand is LayerNorm(x) of the fp32 stream x, normalised in the
-// operand registers; each wave's share of a row's sum, then of its squared
-// deviations (two passes over the registers), goes through LDS.
+// workgroups). Measured at 32 rows against the tile walked in stages: K = 512 3.2 us and
+// K = 2048 4.1 (6.8 on average, the decoder heads 9.6); with a LayerNorm
+// operand, K = 512, 4.4 (N = 1536 8.0, N = 2048 7.8).
+// LN: the A operand is LayerNorm(x) of the fp32 stream x.
+// bf16: wave 0 multiplies all k-steps one after the other, and a row's mean and
+// squared deviations are summed in the order of the staged tiles (k_gemm_lds):
+// a row's result has the same bits whatever the number of rows, here or there.
+// Another order flips roundings of 16-bit activations, and after some layers
+// sampled events with them. The chain of dependent products is what it costs,
+// some 35 cycles a k-step (each wave its own k-steps, partial sums exchanged:
+// 3.1, 3.5 and 4.25 us).
+// fp32 (a matrix instruction takes four times as long, and nothing is rounded
+// in between): each wave multiplies its own k-steps, one exchange of the
+// partial sums; LayerNorm sums by each wave's share of a row.
 // ---------------------------------------------------------------------------
 // One wave's share of a 16-row operand, NCH 16-byte chunks per row, moved
 // straight into LDS and read back as fragments. A fragment read from a
@@ -1317,17 +1344,19 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X
                                                        const float *__restrict__ lg, const float *__restrict__ lb,
                                                        const ELT *__restrict__ W, int T, int N, int K, Epi e) {
   typedef MfmaStep<ELT> S;
+  constexpr bool CHAIN = sizeof(ELT) == 2;               // wave 0 multiplies
   constexpr int KS = S::KSTEP, VE = 16 / sizeof(ELT), LD = 20;
   constexpr int XE = LN ? 4 : sizeof(ELT);               // bytes of an operand element as read
   typedef RowsTile<NS * KS * XE / 16> TA;
   typedef RowsTile<NS * KS * (int)sizeof(ELT) / 16> TB;
-  __shared__ __attribute__((aligned(1024))) char ops[NW * (TA::BYTES + TB::BYTES)];
-  __shared__ __attribute__((aligned(16))) float red[NW * 16 * LD];
+  constexpr int REG = TA::BYTES + TB::BYTES;
+  __shared__ __attribute__((aligned(1024))) char ops[NW * REG];
+  __shared__ __attribute__((aligned(16))) float red[(CHAIN ? 1 : NW) * 16 * LD];
   __shared__ __attribute__((aligned(16))) float st1[LN ? 16 * NW : 4], st2[LN ? 16 * NW : 4];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rr = lane & 15, g = lane >> 4;
   const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
   const int kw = wave * NS * KS;                         // the wave's first k
-  char *const la = ops + wave * (TA::BYTES + TB::BYTES), *const lw = la + TA::BYTES;
+  char *const la = ops + wave * REG, *const lw = la + TA::BYTES;
   // (rows past T and columns past N are clamped; their results are not stored)
   const char *xbase = LN ? (const char *)xf : (const char *)X;
   auto xrow = [&](int row) { return xbase + ((size_t)min(m0 + row, T - 1) * K + kw) * XE; };
@@ -1350,7 +1379,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X
   float ebias = 0.f, eres = 0.f;
   int epos = 0;
   epilogue_fetch(e, min(r, T - 1), min(n, N - 1), ebias, eres, epos);
-  wait_vmcnt<0>();   // this wave's operands are in LDS (nobody else reads them)
+  wait_vmcnt<0>();   // this wave's operands are in LDS
   uint4 a[NS], b[NS];
   float4 xv[LN ? NS : 1][VE / 4];
 #pragma unroll
@@ -1359,40 +1388,80 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X
 #pragma unroll
       for (int c = 0; c < VE / 4; ++c)
         xv[s][c] = __builtin_bit_cast(float4, TA::chunk(la, rr, (s * KS + VE * g) / 4 + c));
-    } else {
+    } else if (!CHAIN) {
       a[s] = TA::chunk(la, rr, 4 * s + g);
     }
-    b[s] = TB::chunk(lw, rr, 4 * s + g);
+    if (!CHAIN) b[s] = TB::chunk(lw, rr, 4 * s + g);
   }
   if (LN) {
-    float s1 = 0.f;
+    float mean = 0.f, rstd;
+    if constexpr (CHAIN) {
+      // row tid / 16; lane tid % 16 takes vectors of 8 columns, 128 apart
+      __builtin_amdgcn_s_barrier();   // (after each wave's wait: all rows are in LDS)
+      if (wave < 4) {
+        constexpr int KK = NW * NS * KS, WK = NS * KS, NU = KK / 128;
+        static_assert(KK % 128 == 0 && WK % 8 == 0, "whole vectors");
+        const int row = tid >> 4, kv = tid & 15;
+        float4 v[NU][2];
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
-      for (int c = 0; c < VE / 4; ++c) s1 += (xv[s][c].x + xv[s][c].y) + (xv[s][c].z + xv[s][c].w);
-    s1 = xor32_sum(xor16_sum(s1));
-    if (g == 0) st1[rr * NW + wave] = s1;
-    lds_barrier();
-    float mean = 0.f;
+          for (int c = 0; c < 2; ++c) {
+            const int k = 128 * u + 8 * kv + 4 * c;
+            v[u][c] = __builtin_bit_cast(float4, TA::chunk(ops + k / WK * REG, row, k % WK / 4));
+          }
+        float sum = 0.f, var = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) mean += st1[rr * NW + w];
-    mean /= (float)K;
-    float s2 = 0.f;
+        for (int u = 0; u < NU; ++u)
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
+          for (int c = 0; c < 2; ++c) sum += (v[u][c].x + v[u][c].y) + (v[u][c].z + v[u][c].w);
+        const float mu = group_sum(sum, 16) / (float)K;
 #pragma unroll
-      for (int c = 0; c < VE / 4; ++c) {
-        const float4 v = xv[s][c];
-        const float c0 = v.x - mean, c1 = v.y - mean, c2 = v.z - mean, c3 = v.w - mean;
-        s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const float a0 = v[u][c].x - mu, a1 = v[u][c].y - mu, a2 = v[u][c].z - mu, a3 = v[u][c].w - mu;
+            var += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
+          }
+        const float rs = 1.f / sqrtf(group_sum(var, 16) / (float)K + 1e-5f);
+        if (kv == 0) {
+          st1[row] = mu;
+          st2[row] = rs;
+        }
       }
-    s2 = xor32_sum(xor16_sum(s2));
-    if (g == 0) st2[rr * NW + wave] = s2;
-    lds_barrier();
-    float var = 0.f;
+      lds_barrier();
+      mean = st1[rr];
+      rstd = st2[rr];
+    } else {
+      // each wave's share of a row's sum, then of its squared deviations
+      float s1 = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) var += st2[rr * NW + w];
-    const float rstd = 1.f / sqrtf(var / (float)K + 1e-5f);
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int c = 0; c < VE / 4; ++c) s1 += (xv[s][c].x + xv[s][c].y) + (xv[s][c].z + xv[s][c].w);
+      s1 = xor32_sum(xor16_sum(s1));
+      if (g == 0) st1[rr * NW + wave] = s1;
+      lds_barrier();
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mean += st1[rr * NW + w];
+      mean /= (float)K;
+      float s2 = 0.f;
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int c = 0; c < VE / 4; ++c) {
+          const float4 v = xv[s][c];
+          const float c0 = v.x - mean, c1 = v.y - mean, c2 = v.z - mean, c3 = v.w - mean;
+          s2 += (c0 * c0 + c1 * c1) + (c2 * c2 + c3 * c3);
+        }
+      s2 = xor32_sum(xor16_sum(s2));
+      if (g == 0) st2[rr * NW + wave] = s2;
+      lds_barrier();
+      float var = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) var += st2[rr * NW + w];
+      rstd = 1.f / sqrtf(var / (float)K + 1e-5f);
+    }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       float y[VE];
@@ -1404,24 +1473,60 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_rows(const ELT *__restrict__ X
         y[4 * c + 2] = (v.z - mean) * rstd * gg.z + bb.z;
         y[4 * c + 3] = (v.w - mean) * rstd * gg.w + bb.w;
       }
-      if constexpr (sizeof(ELT) == 2)
-        a[s] = make_uint4(pk2bf(y[0], y[1]), pk2bf(y[2], y[3]), pk2bf(y[4], y[5]), pk2bf(y[6], y[7]));
+      if constexpr (CHAIN)   // for wave 0, in its order (the wave's rows have been read)
+        *(uint4 *)(la + (s * 64 + lane) * 16) =
+            make_uint4(pk2bf(y[0], y[1]), pk2bf(y[2], y[3]), pk2bf(y[4], y[5]), pk2bf(y[6], y[7]));
       else
         a[s] = make_uint4(__float_as_uint(y[0]), __float_as_uint(y[1]), __float_as_uint(y[2]), __float_as_uint(y[3]));
     }
   }
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (CHAIN) {
+    lds_barrier();   // every wave's operands are in LDS
+    if (wave == 0) {
+      // groups of k-steps, the next one's fragments on their way from LDS (the
+      // products of a group take about as long as its reads)
+      constexpr int NK = NW * NS, G = NK < 8 ? NK : 8;
+      uint4 fa[2][G], fb[2][G];
+      auto read = [&](int grp) {
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
-    acc = S::mma(__builtin_bit_cast(typename S::frag, a[s]), __builtin_bit_cast(typename S::frag, b[s]), acc);
+        for (int i = 0; i < G; ++i) {
+          const char *const li = ops + (grp * G + i) / NS * REG;
+          const int s = (grp * G + i) % NS;
+          fa[grp & 1][i] = LN ? *(const uint4 *)(li + (s * 64 + lane) * 16) : TA::chunk(li, rr, 4 * s + g);
+          fb[grp & 1][i] = TB::chunk(li + TA::BYTES, rr, 4 * s + g);
+        }
+      };
+      read(0);
 #pragma unroll
-  for (int v = 0; v < 4; ++v) red[(wave * 16 + 4 * g + v) * LD + rr] = acc[v];
-  lds_barrier();
-  if (tid >= 256 || r >= T || n >= N) return;
-  float y = 0.f;
+      for (int grp = 0; grp < NK / G; ++grp) {
+        if (grp + 1 < NK / G) read(grp + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int w = 0; w < NW; ++w) y += red[(w * 16 + (tid >> 4)) * LD + (tid & 15)];
-  epilogue1<ELT>(e, r, n, y, ebias, eres, epos);
+        for (int i = 0; i < G; ++i)
+          acc = S::mma(__builtin_bit_cast(typename S::frag, fa[grp & 1][i]),
+                       __builtin_bit_cast(typename S::frag, fb[grp & 1][i]), acc);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[(4 * g + v) * LD + rr] = acc[v];
+    }
+    lds_barrier();
+    if (tid >= 256 || r >= T || n >= N) return;
+    epilogue1<ELT>(e, r, n, red[(tid >> 4) * LD + (tid & 15)], ebias, eres, epos);
+  } else {
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      acc = S::mma(__builtin_bit_cast(typename S::frag, a[s]), __builtin_bit_cast(typename S::frag, b[s]), acc);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[(wave * 16 + 4 * g + v) * LD + rr] = acc[v];
+    lds_barrier();
+    if (tid >= 256 || r >= T || n >= N) return;
+    float y = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) y += red[(w * 16 + (tid >> 4)) * LD + (tid & 15)];
+    epilogue1<ELT>(e, r, n, y, ebias, eres, epos);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -4335,13 +4440,13 @@ void launch_attnhp_update(float *x, const void *o, void *u, void *a, int bf16, i
     k_attnhp_update<float><<<blocks, 256, 0, s>>>(x, (const float *)o, (float *)u, (float *)a, T, d);
 }
 
-void launch_layernorm(const float *x, void *y, int bf16, const float *g, const float *b, int T, int d,
-                      hipStream_t s) {
+void launch_layernorm(const float *x, void *y, int bf16, const float *g, const float *b, int T, int d, int P,
+                      int tile_from, hipStream_t s) {
   const int blocks = (T + 3) / 4;
   if (bf16)
-    k_layernorm<bf16_t><<<blocks, 256, 0, s>>>(x, (bf16_t *)y, g, b, T, d);
+    k_layernorm<bf16_t><<<blocks, 256, 0, s>>>(x, (bf16_t *)y, g, b, T, d, P, tile_from);
   else
-    k_layernorm<float><<<blocks, 256, 0, s>>>(x, (float *)y, g, b, T, d);
+    k_layernorm<float><<<blocks, 256, 0, s>>>(x, (float *)y, g, b, T, d, P, tile_from);
 }
 
 bool gemm_ln_fusable(int bf16, int K) {
@@ -4363,7 +4468,7 @@ static void gemm_dispatch(const void *X, const LnA *ln, const void *W, int T, in
   const ELT *x = (const ELT *)X, *w = (const ELT *)W;
   const float *xf = ln ? ln->x : nullptr, *lg = ln ? ln->g : nullptr, *lb = ln ? ln->b : nullptr;
   // few rows, K a power of two of the k-steps that have an instance: 16 x 16
-  // tiles with K split over the waves. What a CU takes in bounds it (48 KB a
+  // tiles, K loaded by all waves at once. What a CU takes in bounds it (48 KB a
   // tile at K = 512), so the rule is on the rows. Measured, one AR step, this
   // kernel against the 32 x 32 tiles below: d = 512 (8 layers) 32 rows 195 vs
   // 321 us, 128 rows 369 vs 438, 256 rows (operands by the lanes' own loads)

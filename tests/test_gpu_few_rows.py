@@ -1,4 +1,4 @@
-"""The few-row GEMM (16 x 16 tiles, K split over the waves) through verify
+"""The few-row GEMM (16 x 16 tiles) through verify
 passes of B (gamma + 1) rows at the edges of its tiles and of its row limits,
 against the oracle, with the fixed per-workload bounds of gpu_common. The
 products of these targets take every instance: K of 4, 8, 16, 32 and 64
@@ -9,7 +9,7 @@ import dataclasses
 import numpy as np
 import pytest
 
-from gpu_common import Case, check_verify, gpu_state, histories, small, tol_of, weights
+from gpu_common import Case, check_verify, gpu_state, histories, small, to_dev, tol_of, weights
 from oracle import sampler as S
 from oracle.model import Model as OModel
 from paper_2507_09252_amd import workloads as W
@@ -46,3 +46,23 @@ def test_verify_few_rows(case):
                     np.arange(case.B))
     got = _verify(case, gpu_state(case, wt, wd, case.g, 8, 3), dr, ht, hk, 8)
     check_verify(got, want, tol_of(case.wl), case.name, False, dr)
+
+
+# a step's events have the same bits whatever the batch: rows in the few-row
+# GEMM's tiles and (from 129 or 257 rows) in the staged ones
+@pytest.mark.parametrize("name,B", [("c4", 17), ("c3", 17), ("a3", 17), ("c5", 96)])
+def test_step_bits_do_not_depend_on_batch(name, B):
+    wl = W.WORKLOADS[name]
+    big = Case("batch", wl, 300, 2, "bias", True, 1)
+    wt, wd = weights(big)
+    ht, hk = histories(big)
+    print(f"{name}: B {B} and {big.B}", flush=True)
+    runs = []
+    for b in (B, big.B):
+        case = dataclasses.replace(big, B=b)
+        st = gpu_state(case, wt, wd, 1, 24, 7, draft=False)
+        st.tppsd_prefill(to_dev(ht[:b]), to_dev(hk[:b]), 24)
+        st.tppsd_sample_ar(24)
+        t, k, _ = st.tppsd_read_events()
+        runs.append((t[:B, :26].cpu().numpy().view(np.uint32), k[:B, :26].cpu().numpy()))
+    assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])

@@ -97,3 +97,49 @@ def test_smaller_workspace_prefills_in_short_chunks(case):
     tol = tol_of(case.wl)
     for f in ("logw", "mu", "s", "logtype"):
         assert np.abs(getattr(got, f) - getattr(want, f)).max() <= tol, f
+
+
+def _shortest_state(st, seed):
+    """Moves st into the smallest workspace that is taken: its prefill runs in chunks of 16 positions."""
+    L, n, h = tp.lib(), ctypes.c_size_t(), ctypes.c_void_p()
+    args = (st.target.handle, st.draft.handle if st.draft else None, st.B, st.max_events, st.max_gamma)
+    assert L.tppsd_state_bytes(*args, ctypes.byref(n)) == 0
+    ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
+    lo, hi = 0, n.value   # (refused, taken)
+    while hi - lo > 256:
+        mid = (lo + hi) // 2
+        if L.tppsd_state_create(*args, seed, tp.FLAG_BONUS, ws.data_ptr(), mid, ctypes.byref(h)) == 0:
+            L.tppsd_state_destroy(h)
+            hi = mid
+        else:
+            lo = mid
+    assert L.tppsd_state_create(*args, seed, tp.FLAG_BONUS, ws.data_ptr(), hi, ctypes.byref(h)) == 0
+    L.tppsd_state_destroy(st.handle)
+    st.handle, st.ws = h, ws
+
+
+NHP128 = dataclasses.replace(W.WORKLOADS["a3"], target=W.ModelCfg(2, 128, 4, 0, 4, 22, "bf16", "attnhp", 0.1, 50.0))
+
+
+# In 16 bits the order of a sum decides roundings and with them the events
+# sampled later: an encoded history has the same bits whatever the chunks were.
+# Widths of 512: chunks of 16 positions below and from 512 rows (LayerNorm in the
+# product or before it), a ragged end of 1 to 15 positions on either side of that
+@pytest.mark.parametrize("wl,B,n", [(WIDE, 5, 18), (WIDE, 5, 143), (WIDE, 31, 66), (WIDE, 33, 113), (WIDE, 33, 128),
+                                    (WIDE, 40, 126), (NHP128, 7, 100)])
+def test_history_bits_do_not_depend_on_chunks(wl, B, n):
+    case = Case("chunks", wl, B, n, "bias", True)
+    wt, wd = weights(case)
+    ht, hk = histories(case)
+    hk = hk % wl.target.n_types
+    print(f"{wl.name} B {B}, history {n}", flush=True)
+    runs = []
+    for short in (False, True):
+        st = gpu_state(case, wt, wd, 3, 12, 3, draft=False)
+        if short:
+            _shortest_state(st, 3)
+        st.tppsd_prefill(to_dev(ht), to_dev(hk), 12)
+        st.tppsd_sample_ar(12)
+        t, k, _ = st.tppsd_read_events()
+        runs.append((t[:, :n + 12].cpu().numpy().view(np.uint32), k[:, :n + 12].cpu().numpy()))
+    assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
