@@ -33,10 +33,11 @@
 //    forms the record.
 // Measured, 10 drafts (before: one workgroup with weights in LDS or L2, for
 // AttNHP the per-step kernels): fp32 d = 32, 64 sequences of 40 events 118 ->
-// 56 us; bf16 d = 64, two layers, 256 sequences of 576 events 333 -> 167 us (of
+// 56 us; bf16 d = 64, two layers, 256 sequences of 576 events 333 -> 178 us (of
 // these some 95 us are the cache at 8 TB/s); AttNHP d = 64, two layers, 256
 // sequences of 580 events 417 -> 146 us.
-// Rounding points are those of the layered kernels.
+// Rounding points are those of the layered kernels, but for THP's attention
+// probabilities, which are not rounded (as in the other one-launch kernels).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -73,8 +74,13 @@ template <> struct DgFrag<float> {
 // bf16: MFMA. Lane (r, g) holds dims 4 g .. + 3 of keys 16 m + r (m = 0..3) and,
 // as the value operand, positions 32 c + 8 g .. + 7 of column r; group m's
 // product puts the queries in rows 4 m, 4 m + 1 of its first operand, so that
-// lane (r, g) ends up with the scores of key 16 g + r. The probabilities' sum
-// is a product with ones.
+// lane (r, g) ends up with the scores of key 16 g + r. THP's probabilities stay
+// in fp32, as the other one-launch drafting kernels have them: each is cut into
+// three bf16 parts, which hold all of its 24 bits, with a product each (the
+// three sums do not wait for one another). AttNHP's are rounded to bf16, as in
+// the layered kernels that serve its other sizes. Their sum is kept by the lane.
+// (Ten drafts of 256 sequences after 576 events, d = 64, two layers: 178 us,
+// with rounded probabilities 169.)
 // fp32: vector ALU (an fp32 matrix instruction with one query in 16 rows takes
 // eight times the cycles of the FMAs): lane holds its key's row and, for the
 // value sums, positions 16 g + s of column r.
@@ -125,10 +131,12 @@ template <> struct DgStep<float> {
 };
 
 // the one or two queries of a wave's head and their running sums
-template <typename ELT> struct DgAttn;
-template <> struct DgAttn<bf16_t> {
+// NPL: parts of a bf16 kernel's probability
+template <typename ELT, int NPL> struct DgAttn;
+template <int NPL> struct DgAttn<bf16_t, NPL> {
   uint2 q[4];
-  f32x4_t o, l;
+  f32x4_t o[NPL];
+  float l[2];
   // qs: query rows in LDS, this head's 16 dims
   __device__ __forceinline__ void init(const bf16_t *q0, int ld, int P, int lane) {
     const int rr = lane & 15, g = lane >> 4;
@@ -138,7 +146,9 @@ template <> struct DgAttn<bf16_t> {
       const bool in = (rr >> 2) == m && (rr & 3) < P;
       q[m] = make_uint2(in ? qv.x : 0u, in ? qv.y : 0u);
     }
-    o = l = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) o[i] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    l[0] = l[1] = 0.f;
   }
   __device__ __forceinline__ void scores(const DgStep<bf16_t> &st, int P, float &s0, float &s1) const {
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -151,15 +161,28 @@ template <> struct DgAttn<bf16_t> {
   }
   __device__ __forceinline__ void rescale(float a0, float a1, int lane) {
     const float a = (lane & 15) == 1 ? a1 : a0;   // column r is query r
-    o *= a;
-    l *= a;
+#pragma unroll
+    for (int i = 0; i < NPL; ++i) o[i] *= a;
+    l[0] *= a0, l[1] *= a1;
   }
-  // p: the queries' rows of probabilities in LDS; nv: valid positions of the step
-  __device__ __forceinline__ void apply(const DgStep<bf16_t> &st, const bf16_t *p, int ldp, int P, int nv, int lane) {
+  // the lane's probability of a step for query t, to the parts' rows (ldl apart)
+  __device__ __forceinline__ void keep(int t, float p, bf16_t *row, int ldl) {
+    if constexpr (NPL == 1) {
+      *row = f2bf(p);
+      l[t] += rnd_act<bf16_t>(p);
+    } else {
+      const float m = p - __uint_as_float(__float_as_uint(p) & 0xFFFF0000u);
+      const float s = m - __uint_as_float(__float_as_uint(m) & 0xFFFF0000u);
+      row[0] = (bf16_t)(__float_as_uint(p) >> 16);
+      row[ldl] = (bf16_t)(__float_as_uint(m) >> 16);
+      row[2 * ldl] = (bf16_t)(__float_as_uint(s) >> 16);
+      l[t] += p;
+    }
+  }
+  // p: the queries' rows of probabilities in LDS (parts ldl apart); nv: valid positions of the step
+  __device__ __forceinline__ void apply(const DgStep<bf16_t> &st, const bf16_t *p, int ldl, int P, int nv, int lane) {
     const int rr = lane & 15, g = lane >> 4;
-    const bf16x8_t ones =
-        __builtin_bit_cast(bf16x8_t, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
-    const bf16_t *pr = p + min(rr, P - 1) * ldp + 8 * g;
+    const bf16_t *pr = p + min(rr, P - 1) * NPL * ldl + 8 * g;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       u32x4_t w = {st.v[c].x, st.v[c].y, st.v[c].z, st.v[c].w};
@@ -168,21 +191,27 @@ template <> struct DgAttn<bf16_t> {
 #pragma unroll
         for (int i = 0; i < 4; ++i) w[i] = 2 * i >= n8 ? 0u : (2 * i + 1 >= n8 ? w[i] & 0xFFFFu : w[i]);
       }
-      const bf16x8_t pb = *(const bf16x8_t *)(pr + 32 * c);
-      l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, l, 0, 0, 0);
-      o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), pb, o, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NPL; ++i)
+        o[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w),
+                                                       *(const bf16x8_t *)(pr + i * ldl + 32 * c), o[i], 0, 0, 0);
     }
   }
   // r: [2][ld] per query (max, sum, -, -, 16 sums)
   __device__ __forceinline__ void finish(float *r, int ld, int P, int lane) const {
     const int rr = lane & 15, g = lane >> 4;
-    if (rr < P) {
-      *(f32x4_t *)(r + rr * ld + 4 + 4 * g) = o;
-      if (g == 0) r[rr * ld + 1] = l[0];
+    f32x4_t sum = o[0];
+    if constexpr (NPL == 3) sum += o[1] + o[2];
+    if (rr < P) *(f32x4_t *)(r + rr * ld + 4 + 4 * g) = sum;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      if (t >= P) break;
+      const float sl = lanes_sum<64>(l[t]);
+      if (lane == 0) r[t * ld + 1] = sl;
     }
   }
 };
-template <> struct DgAttn<float> {
+template <int NPL> struct DgAttn<float, NPL> {
   float4 q0[4];
   const float *q1;   // the second query's row, read where it is used
   float o[2], l[2];
@@ -212,6 +241,7 @@ template <> struct DgAttn<float> {
     o[0] *= a0, l[0] *= a0;
     o[1] *= a1, l[1] *= a1;
   }
+  __device__ __forceinline__ void keep(int, float p, float *row, int) { *row = p; }
   // (values past the range were clamped to its last position: finite, times a probability of 0)
   __device__ __forceinline__ void apply(const DgStep<float> &st, const float *p, int ldp, int P, int nv, int lane) {
     const int g = lane >> 4;
@@ -298,6 +328,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
   typedef DgFrag<ELT> X;
   typedef typename X::frag frag;
   typedef DgTile<ELT> Tile;
+  constexpr int NPL = sizeof(ELT) == 2 && F != 0 ? 3 : 1;
   constexpr int NE = Tile::NE;
   constexpr bool NHP = F == 0;
   constexpr int KS = S::KSTEP, VE = 16 / sizeof(ELT), DH = 16, H = D / 16;
@@ -319,7 +350,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
   __shared__ __attribute__((aligned(16))) float pA[KGO][2][D], pB[KGF][2][D], zs[2][D];
   __shared__ __attribute__((aligned(16))) ELT as[NW][2][D];   // each wave's operand rows
   __shared__ __attribute__((aligned(16))) float pm[NW][2][DH + 4];
-  __shared__ __attribute__((aligned(16))) ELT qs[2][D], hs[2][NHP ? 4 : F], es[4 * D], pbuf[NW][2][NB * 64];
+  __shared__ __attribute__((aligned(16))) ELT qs[2][D], hs[2][NHP ? 4 : F], es[4 * D], pbuf[NW][2][NPL][NB * 64];
   __shared__ __attribute__((aligned(16))) ELT kt_s[L][H][DG_TAIL * DH], vt_s[L][H][DG_TAIL * DH];
   __shared__ __attribute__((aligned(16))) float vec[L * LV + 4 * D + DG_HEAD_TILES * 16], hv[DG_HEAD_TILES * 16];
   __shared__ __attribute__((aligned(16))) ELT emb[TPPSD_MAX_TYPES * D];
@@ -580,7 +611,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
       phase();
       // ---- attention: this wave's share of its head's keys ------------------
       {
-        DgAttn<ELT> at;
+        DgAttn<ELT, NPL> at;
         at.init(&qs[0][16 * head], D, P, lane);
         float m_run[2] = {-INFINITY, -INFINITY};
         // ns steps whose scores are in sc: running maxima, rescaled sums, probabilities to LDS
@@ -593,16 +624,20 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
 #pragma unroll
             for (int i = 1; i < NB; ++i) mx = fmaxf(mx, sc[p][i]);
             const float m_new = fmaxf(m_run[p], lanes_max(mx));
-            const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-            al[p] = exp_score<ELT>(m_run[p] - m_ref);
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-              if (i >= ns) break;   // uniform
-              st(&pbuf[wave][p][0], 64 * i + lane, exp_score<ELT>(sc[p][i] - m_ref));
-            }
+            al[p] = exp_score<ELT>(m_run[p] - (m_new == -INFINITY ? 0.f : m_new));
             m_run[p] = m_new;
           }
           at.rescale(al[0], al[1], lane);
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            if (p >= P) break;
+            const float m_ref = m_run[p] == -INFINITY ? 0.f : m_run[p];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+              if (i >= ns) break;   // uniform
+              at.keep(p, exp_score<ELT>(sc[p][i] - m_ref), &pbuf[wave][p][0][64 * i + lane], NB * 64);
+            }
+          }
           wave_lds_order();
         };
         const int nbt = (mine + NB - 1) / NB;
@@ -626,7 +661,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
           for (int i = 0; i < NB; ++i) {
             const int idx = bt * NB + i;
             if (idx >= mine) break;   // uniform
-            at.apply(kv[i], &pbuf[wave][0][64 * i], NB * 64, P, base - 64 * (sub + WPH * idx), lane);
+            at.apply(kv[i], &pbuf[wave][0][0][64 * i], NB * 64, P, base - 64 * (sub + WPH * idx), lane);
           }
           wave_lds_order();
           fetch_v(more ? ly : nly, more ? bt + 1 : 0);
@@ -644,7 +679,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
           sc[0][0] = in_cap && lane <= off0 ? s0 * scale : -INFINITY;
           sc[1][0] = in_cap && lane <= off0 + 1 ? s1 * scale : -INFINITY;
           softmax(sc, 1);
-          at.apply(tl, &pbuf[wave][0][0], NB * 64, P, 64, lane);
+          at.apply(tl, &pbuf[wave][0][0][0], NB * 64, P, 64, lane);
           wave_lds_order();
         }
         at.finish(&pm[wave][0][0], DH + 4, P, lane);

@@ -62,3 +62,23 @@ def test_draft_regs(case):
     tol = 1e-5 if case.wl.prec == "fp32" else 2e-3
     compared = check_draft_record(D, ost, draft_out(dbuf, rows, g), g, seed, 0, rows, tol, case.name)
     assert compared >= 0.9 * case.B * g
+
+
+# THP's attention probabilities stay in fp32: the mixtures of the first draft
+# agree with the wave-per-sequence kernel's, which serves the next larger batch,
+# to the last bits of the sums and a few 16-bit roundings of activations that
+# these tip (measured 5.5e-8 and 8.1e-8, relative 2-norm; with probabilities
+# rounded to bf16, as many roundings as keys, 3.2e-6)
+def test_draft_probabilities_are_not_rounded():
+    wl = W.WORKLOADS["c5"]
+    ht, hk = W.make_histories(wl, batch=513, n_hist=200)
+    wt, wd = W.workload_weights(wl, init="bias")
+    M, K, out = wl.target.n_mix, wl.target.n_types, []
+    for B in (512, 513):
+        st = tp.State(tp.Model(wl.target, wt), tp.Model(wl.draft, wd), B, 260, 4, seed=1)
+        st.tppsd_prefill(to_dev(ht[:B]), to_dev(hk[:B]), 50)
+        buf = tp.DraftBuffers(B, 4, M, K)
+        st.tppsd_draft(4, buf)
+        out.append([x[:512, 0].double().cpu() for x in (buf.mix, buf.logtype)])
+    for a, b in zip(*out):
+        assert (a - b).norm() / a.norm() < 1e-6
