@@ -250,6 +250,7 @@ struct tppsd_state {
   tppsd_accept_buf iac{};
   // host-side run state
   int n_gen = 0;
+  int job_ctx = 0;                 // events per sequence half-way through the job of the last prefill
   int left_max = -1;               // events the slowest sequence still needs, -1: not known here
   bool windowed = false;           // end times given: a sequence may finish at any event
   bool prefilled = false, draft_ok = false, drafted_this_round = false;
@@ -877,7 +878,8 @@ int do_draft_poisson(tppsd_state *s, int gamma, const float *params, const tppsd
 // after the pending event
 bool seq_pass_ok(const tppsd_state *s, int P) {
   const tppsd_model *m = s->T;
-  return !m->attnhp() && verify_seq_ok(m->bf16(), m->cfg.n_layers, m->d(), m->H(), m->cfg.d_ffn, P, s->kv_cap);
+  return !m->attnhp() &&
+         verify_seq_ok(m->bf16(), m->cfg.n_layers, m->d(), m->H(), m->cfg.d_ffn, s->B, P, s->job_ctx);
 }
 
 void seq_pass(tppsd_state *s, int P, const HeadArgs &h, const float *dr_t, const int32_t *dr_k, int dr_stride,
@@ -1377,6 +1379,7 @@ int tppsd_prefill_window(tppsd_state *s, const float *d_t, const int32_t *d_k, i
   s->n_gen = n_gen;
   s->windowed = d_t_end != nullptr;
   s->left_max = s->windowed ? -1 : n_gen;
+  s->job_ctx = n0 + n_gen / 2;
   if (!s->heads_built) {
     for (int which = 0; which < (s->D ? 2 : 1); ++which) {
       const tppsd_model *m = which ? s->D : s->T;
@@ -1624,9 +1627,9 @@ int tppsd_sample_ar(tppsd_state *s, int n_events, float *d_t_out, int32_t *d_k_o
     return hip_check("tppsd_sample_ar");
   }
   {
-    // graphs embed the output pointers, their stride and n_gen
-    const long long key = ((long long)(uintptr_t)d_t_out * 31 + (long long)(uintptr_t)d_k_out) * 131 +
-                          (long long)n_events * 1000003LL + s->n_gen;
+    // graphs embed the output pointers, their stride, n_gen and the kind of pass
+    const long long key = (((long long)(uintptr_t)d_t_out * 31 + (long long)(uintptr_t)d_k_out) * 131 +
+                           (long long)n_events * 1000003LL + s->n_gen) * 2 + seq_pass_ok(s, 1);
     for (int w = 0; w < 2; ++w) {
       if (s->ar_exec[w] && s->ar_key[w] == key) continue;
       drop_graph(&s->ar_exec[w]);
@@ -1725,7 +1728,7 @@ int sd_loop(tppsd_state *s, int gamma, const float *params, int max_rounds, int 
   const bool kern = (s->timing & TPPSD_TIME_KERNELS) != 0;
   const bool phases = (s->timing & TPPSD_TIME_PHASES) != 0;
   const bool graphs = !kern;
-  const long long key = (long long)gamma * 100000007LL + s->n_gen;
+  const long long key = ((long long)gamma * 100000007LL + s->n_gen) * 2 + seq_pass_ok(s, gamma + 1);
   if (graphs && !phases && (!s->sd_exec[0] || s->sd_key != key || s->sd_params != params)) {
     drop_graph(&s->sd_exec[0]);
     s->sd_key = -1;

@@ -262,8 +262,9 @@ struct VerifySeqArgs {
   uint32_t *status;
   HeadArgs h;               // HEAD_VERIFY, or HEAD_AR (P = 1)
 };
-// whether k_verify_seq serves a THP target of these sizes for P positions over caches of kv_cap
-bool verify_seq_ok(int bf16, int L, int d, int H, int F, int P, int kv_cap);
+// whether k_verify_seq serves a THP target of these sizes for P positions of B sequences with
+// some ctx events each
+bool verify_seq_ok(int bf16, int L, int d, int H, int F, int B, int P, int ctx);
 void launch_verify_seq(const VerifySeqArgs &a, int B, int bf16, hipStream_t st, hipEvent_t ev0 = nullptr,
                        hipEvent_t ev1 = nullptr);
 

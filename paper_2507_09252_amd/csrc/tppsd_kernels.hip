@@ -4007,19 +4007,28 @@ __global__ __launch_bounds__(512) void k_verify_seq(VerifySeqArgs a) {
   for (int r = wave; r < P; r += NW) head_row(hv + r * LV, M, K, a.h, b, r);
 }
 
-bool verify_seq_ok(int bf16, int L, int d, int H, int F, int P, int kv_cap) {
-  // instantiated widths, d_head 16, one tile of 16 positions. At d = 32 always;
-  // at d = 64 while the contexts are short: a sequence's caches stream through
-  // one CU here, and through a workgroup per head in the layered pass. Measured,
-  // d = 64 / F = 256, 4 layers, 64 sequences x 11 positions after 100 / 600 / 2500
-  // events, this kernel against the layered pass: fp32 48 / 87 / 248 vs 87 / 110
-  // / 175 us, bf16 28 / 45 / 107 vs 61 / 72 / 91; 16 sequences: fp32 48 / 85 /
-  // 240 vs 76 / 90 / 114, bf16 27 / 41 / 106 vs 80 / 87 / 106; 1024 sequences
-  // after 600 events fp32 380 vs 494. A job's average context is about half of
-  // the capacity, which is what the host knows
-  const bool widths = (d == 32 && (F == 64 || F == 128)) ||
-                      (d == 64 && (F == 128 || F == 256) && kv_cap <= (bf16 ? 4096 : 1024));
-  return widths && d == 16 * H && L <= FD_MAX_LAYERS && P <= 16;
+bool verify_seq_ok(int bf16, int L, int d, int H, int F, int B, int P, int ctx) {
+  // instantiated widths, d_head 16, one tile of 16 positions
+  if (!(d == 32 && (F == 64 || F == 128)) && !(d == 64 && (F == 128 || F == 256))) return false;
+  if (d != 16 * H || L > FD_MAX_LAYERS || P > 16) return false;
+  // Measured, us, this kernel against the layered pass (d = 64: F = 256, 4 layers; d = 32: F = 64, 2 layers; 11
+  // positions, or an AR step).
+  // A sequence costs a whole 16-position tile here, so past two sequences per CU few positions are the layered
+  // pass's: 512 sequences after 200 events 117 vs 185, AR 119 vs 158 (fp32 d = 64); 65 vs 91, AR 67 vs 84 (bf16);
+  // 2048 sequences 449 vs 570, 5 positions 434 vs 450, AR 462 vs 376; 247 vs 257, 5 positions 233 vs 197, AR 262
+  // vs 163; d = 32 fp32 150 vs 151, AR 166 vs 110; bf16 107 vs 84, AR 98 vs 53
+  if (B > 512 && !(P >= 8 && (d == 64 || !bf16))) return false;
+  // A sequence's caches stream through one CU here, in the layered pass through a workgroup or more per head: the
+  // fewer sequences, the shorter the contexts from which that is faster. fp32 d = 64, 1 / 64 / 128 sequences: after
+  // 400 events 71 vs 85 / 73 vs 99 / 82 vs 114 (500), after 700 93 vs 86 / 97 vs 113 / -, after 1000 116 vs 84 /
+  // 121 vs 124 / 126 vs 142, after 2000 197 vs 101 / 200 vs 153 / 210 vs 209; AR after 400 73 vs 73 / 77 vs 85 /
+  // 87 vs 110 (500), after 1000 119 vs 90 / 125 vs 116 / 128 vs 135. fp32 d = 32, AR: after 1000 37 vs 42 / 40 vs
+  // 54, after 1500 47 vs 45 / 50 vs 59, after 2000 56 vs 41 / 59 vs 61. bf16 d = 64, 1 / 64: after 1500 67 vs 95
+  // / 73 vs 80, after 2000 81 vs 90 / 90 vs 85, after 3000 111 vs 94 / 122 vs 95; bf16 d = 32: after 2000 29 vs
+  // 36 / 32 vs 41, AR after 3000 36 vs 32 / 42 vs 48
+  const int most = bf16 ? (d == 64 ? 1800 : 2400)
+                        : std::min(2000, d == 32 ? 1400 + 12 * B : P == 1 ? 380 + 6 * B : 550 + 9 * B);
+  return ctx <= most;
 }
 
 void launch_verify_seq(const VerifySeqArgs &a, int B, int bf16, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {

@@ -68,3 +68,29 @@ def test_ar_step_seq(case):
     compared, generated = replay_ar_steps(case, OModel(case.wl.target, wt), st, 9, 12)
     assert st.tppsd_state_status()["bits"] == 0
     assert compared >= 0.5 * generated, (compared, generated)
+
+
+# which pass serves a job depends on its events, not on the state's capacity: the
+# per-sequence pass has no attention launches of its own
+@pytest.mark.parametrize("prec,B,n,n_gen,cap,per_seq", [
+    ("fp32", 3, 40, 24, 4200, True), ("bf16", 3, 40, 24, 9000, True), ("fp32", 3, 900, 24, 960, False),
+    ("bf16", 3, 1900, 24, 1960, False), ("fp32", 3, 380, 600, 1024, False), ("fp32", 80, 900, 24, 960, True)])
+def test_pass_follows_the_job(prec, B, n, n_gen, cap, per_seq):
+    from gpu_common import to_dev
+    from paper_2507_09252_amd import tppsd as tp
+    case = _case(prec, 64, 256, 2, 5, 3, n, 4, B)
+    wt, wd = weights(case)
+    ht, hk = histories(case)
+    print(case.name, flush=True)
+    st = tp.State(tp.Model(case.wl.target, wt), tp.Model(case.wl.draft, wd), B, cap, 4, seed=1)
+    st.tppsd_prefill(to_dev(ht), to_dev(hk % 3), n_gen)
+    st.tppsd_timing_enable(tp.TIME_KERNELS)
+    st.tppsd_sample_sd(4, max_rounds=2)
+    tm = st.tppsd_timing_read()
+    st.tppsd_timing_enable(0)
+    assert (tm["attn_launches"] == 0) == per_seq, tm
+    # the same state, a short job: its graphs are of the other pass
+    for job in ((8, 16), (n, n_gen)):
+        st.tppsd_prefill(to_dev(ht[:, :job[0]]), to_dev(hk[:, :job[0]] % 3), job[1])
+        st.tppsd_sample_sd(4)
+        assert st.tppsd_state_status()["n_done"] == B
