@@ -72,14 +72,19 @@ size_t prefill_rows(int B, int cap) {
   return (size_t)B * std::min<size_t>(want, std::max(cap, PREFILL_CHUNK));
 }
 
-// Verify attention of caches of 512 MiB and more over all layers reads keys
-// and values with the non-temporal hint: nothing of them is left in the 256 MB
-// last-level cache by the next pass, and passing by they push out weights and
-// rows (per pass: 970 MB of d = 256 395 -> 366 us, 1.4 GB of d = 512 550 ->
-// 517, 397 MB of capacity at d = 128 225 -> 223). Smaller caches are found
-// there again (402 MB of capacity 294 -> 298 us, 332 MB 264 -> 282, 201 MB 173
-// -> 187). Returns launch_attention's verify argument.
-int verify_role(int L, size_t layer_bytes) { return 2 * (size_t)L * layer_bytes >= (size_t)512 << 20 ? 2 : 1; }
+// Events per sequence from which verify attention reads keys and values with the
+// non-temporal hint: where those of all layers and sequences are 384 MiB, next to
+// nothing of them is left in the 256 MB last-level cache by the next pass, and
+// passing by they push out weights and rows. The kernel compares with the
+// sequence's own events, so that the first rounds of a long job still find their
+// caches on chip. Measured, us per pass, plain / with the hint, 200, 270, 400 and
+// 700 MB of keys and values after 300 events: d = 256 253 / 271, 294 / 304, 287 /
+// 274, 406 / 384; d = 128 212 / 234, 248 / 268, 306 / 310, 337 / 318; d = 512 385
+// / 395, 424 / 416, 586 / 563, 811 / 764 (after 1500 events, 8 to 28 sequences,
+// 368 / 390, 406 / 405, 431 / 437, 517 / 513).
+int attn_nt_keys(int B, int L, int d) {
+  return (int)std::min<size_t>((((size_t)384 << 20) - 1) / ((size_t)4 * L * B * d) + 1, INT32_MAX);
+}
 
 // ---- packed weight layout -------------------------------------------------
 struct Entry {
@@ -439,6 +444,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
   const int B = s->B, d = m->d(), H = m->H(), dh = m->dh(), F = m->cfg.d_ffn, bf = m->bf16();
   const int T = B * P, L = m->cfg.n_layers;
   const bool timed = verify && s->cur_ev != nullptr;
+  const int nt_keys = attn_nt_keys(B, L, d);
   auto ev = [&](int pair, int end) -> hipEvent_t {
     if (!timed) return nullptr;
     s->ev_used[pair] = 1;
@@ -471,7 +477,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
       launch_gemm(s->u, nullptr, w.qkv_w, bf, T, 3 * d, 2 * d, e, st, ev(L + 4 * l, 0), ev(L + 4 * l, 1));
       if (!head && l + 1 == L) break;   // (prefill: past the last layer's keys and values nothing is used)
       launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                       1, verify ? verify_role(L, c.layer_bytes) : 0, ev(l, 0), ev(l, 1), st);
+                       1, verify, nt_keys, ev(l, 0), ev(l, 1), st);
       launch_attnhp_update(s->x, s->o, s->u, s->a, bf, T, d, st);
     }
   }
@@ -533,7 +539,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
       const bool last = l + 1 == L;
       if (last && !head) break;
       launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                       0, verify ? verify_role(L, c.layer_bytes) : 0, ev(l, 0), ev(l, 1), st);
+                       0, verify, nt_keys, ev(l, 0), ev(l, 1), st);
       const LayerW &w = m->layers[l];
       ba.first = 0;
       ba.pre = 1;
@@ -603,7 +609,7 @@ int forward(tppsd_state *s, const tppsd_model *m, const ModelCache &c, const int
     }
     if (!head && l + 1 == L) break;   // (prefill: past the last layer's keys and values nothing is used)
     launch_attention(s->q, kc, vc, s->o, bf, start, start_off, s->done, B, P, H, dh, s->kv_cap, s->attn_part,
-                     0, verify ? verify_role(L, c.layer_bytes) : 0, ev(l, 0), ev(l, 1), st);
+                     0, verify, nt_keys, ev(l, 0), ev(l, 1), st);
     if (use_layer_fused) {
       LayerArgs la{};
       la.x = s->x;

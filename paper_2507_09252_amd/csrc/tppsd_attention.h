@@ -34,9 +34,10 @@ inline size_t attn_part_floats(int B, int H, int dh, int qtiles_max, int max_key
 // k_attn_rows, which splits the queries instead of the keys and has no partials.
 constexpr int ATTN_ROWS_MIN_P = 16;
 // sink: AttNHP normalisation 1 + sum f (an extra key of score 0, value 0);
-// verify: 1 = the verify pass, 2 = with non-temporal cache loads (bf16), 0 = other
+// verify: the verify pass, whose bf16 form reads a sequence's keys and values with
+// the non-temporal hint from nt_keys of them on
 void launch_attention(const void *q, const void *kc, const void *vc, void *o, int bf16,
                       const int32_t *start, int start_off, const int32_t *done, int B, int P, int H,
-                      int dh, int cap, float *part, int sink, int verify, hipEvent_t ev0, hipEvent_t ev1,
-                      hipStream_t st);
+                      int dh, int cap, float *part, int sink, int verify, int nt_keys, hipEvent_t ev0,
+                      hipEvent_t ev1, hipStream_t st);
 }  // namespace tppsd

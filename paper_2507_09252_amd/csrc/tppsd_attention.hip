@@ -6,6 +6,7 @@
 #include <math.h>
 #include <stdlib.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "tppsd_device.h"
 
@@ -18,8 +19,8 @@ namespace tppsd {
 // 0 .. start[b] + start_off + p. Online softmax over 64-key tiles.
 // ---------------------------------------------------------------------------
 
-// ROLE: 1 = verify pass of the target, 2 = the same with non-temporal loads of
-// keys and values (bf16; caches too large to stay on the chip), 0 = other
+// ROLE: 1 = verify pass of the target (bf16: keys and values of long contexts
+// are read with the non-temporal hint, see attn_nt_keys), 0 = other
 // passes), so that profiles report the verify launches under their own name.
 // AttNHP attention (App. D.4) divides by 1 + sum f instead of sum f: the same
 // as one more key of score 0 and value 0. Applied once, where the softmax
@@ -48,7 +49,7 @@ __device__ __forceinline__ void sink_adjust(float &M, float &L, float &O) {
 // operand of O^T = V^T P^T. The A operand (8 consecutive keys of one value
 // column) is one 16-byte load from the position-blocked value cache.
 
-template <bool NT> __device__ __forceinline__ bf16x8_t ld_kv(const bf16x8_t *p) {
+template <bool NT, typename T> __device__ __forceinline__ T ld_kv(const T *p) {
   return NT ? __builtin_nontemporal_load(p) : *p;
 }
 
@@ -60,7 +61,7 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
                                                    const int32_t *__restrict__ done, int start_off,
                                                    const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc,
                                                    const bf16_t *__restrict__ vc, bf16_t *__restrict__ o, int cap,
-                                                   int splits, float *__restrict__ part, int sink) {
+                                                   int splits, float *__restrict__ part, int sink, int nt_keys) {
   constexpr int KT = 32, NDT = DH / 16, NC = DH >= 32 ? DH / 32 : 1, NQ = 16 * QT;
   static_assert(NW == 4 || NW == 8, "four or eight waves");
   __shared__ float red_m[4][NQ], red_l[4][NQ];
@@ -117,100 +118,105 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
   // permuted key rows of the two S^T halves loaded by this lane
   const int krow0 = 8 * (rr >> 2) + (rr & 3), krow1 = krow0 + 4;
 
-  for (int kt = k_begin + wave * KT; kt < k_end; kt += NW * KT) {
-    const bool interior = kt + KT <= k_end && kt + KT <= base + 1;   // every key visible to every query
-    const size_t r0 = kvbase + min(kt + krow0, cap - 1), r1 = kvbase + min(kt + krow1, cap - 1);
-    bf16x8_t a0[NC], a1[NC];
-    short4_t b0 = {0, 0, 0, 0}, b1 = {0, 0, 0, 0};
-    if (DH >= 32) {
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        a0[c] = ld_kv<ROLE == 2>((const bf16x8_t *)(kc + r0 * DH + 32 * c + 8 * g));
-        a1[c] = ld_kv<ROLE == 2>((const bf16x8_t *)(kc + r1 * DH + 32 * c + 8 * g));
-      }
-    } else {
-      b0 = *(const short4_t *)(kc + r0 * DH + 4 * g);
-      b1 = *(const short4_t *)(kc + r1 * DH + 4 * g);
-    }
-    // values of keys kt + 8 g .. + 7, columns 16 td + rr; blocks past the key
-    // range read the range's last block (unconditional loads: a load under a
-    // lane condition makes the compiler wait for every load before it), and
-    // positions past the range are zeroed (never-written cache slots may hold
-    // NaN bits)
-    const int k8 = kt + 8 * g, nv = k_end - k8;
-    const int k8c = min(k8, (k_end - 1) & ~7);
-    uint4 vw[NDT];
-#pragma unroll
-    for (int td = 0; td < NDT; ++td)
-      vw[td] = __builtin_bit_cast(uint4, ld_kv<ROLE == 2>((const bf16x8_t *)(vc + kvbase * DH + (size_t)(k8c >> 3) * (8 * DH) +
-                                                                       (16 * td + rr) * 8)));
-    if (!interior && nv < 8) {
-#pragma unroll
-      for (int td = 0; td < NDT; ++td) {
-        uint32_t w[4] = {vw[td].x, vw[td].y, vw[td].z, vw[td].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (2 * i >= nv) w[i] = 0u;
-          else if (2 * i + 1 >= nv) w[i] &= 0xFFFFu;
-        }
-        vw[td] = (uint4){w[0], w[1], w[2], w[3]};
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+  auto steps = [&](auto nt) {
+    constexpr bool NT = decltype(nt)::value;
+    for (int kt = k_begin + wave * KT; kt < k_end; kt += NW * KT) {
+      const bool interior = kt + KT <= k_end && kt + KT <= base + 1;   // every key visible to every query
+      const size_t r0 = kvbase + min(kt + krow0, cap - 1), r1 = kvbase + min(kt + krow1, cap - 1);
+      bf16x8_t a0[NC], a1[NC];
+      short4_t b0 = {0, 0, 0, 0}, b1 = {0, 0, 0, 0};
       if (DH >= 32) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[c], qf[t][c], s0, 0, 0, 0);
-          s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[c], qf[t][c], s1, 0, 0, 0);
+          a0[c] = ld_kv<NT>((const bf16x8_t *)(kc + r0 * DH + 32 * c + 8 * g));
+          a1[c] = ld_kv<NT>((const bf16x8_t *)(kc + r1 * DH + 32 * c + 8 * g));
         }
       } else {
-        s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b0, qf16[t], s0, 0, 0, 0);
-        s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b1, qf16[t], s1, 0, 0, 0);
+        b0 = ld_kv<NT>((const short4_t *)(kc + r0 * DH + 4 * g));
+        b1 = ld_kv<NT>((const short4_t *)(kc + r1 * DH + 4 * g));
       }
-      // scores of keys kt + 8g + j, j = 0..7, for query 16 t + rr (steps
-      // wholly inside every query's visible range skip the masks; padding
-      // queries then carry finite scores of zero queries, never stored)
-      const int my_q = 16 * t + rr, my_last = base + my_q;
-      const bool q_ok = my_q < P;
-      float sv[8];
-      float mx = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int key = kt + 8 * g + j;
-        const float raw = (j < 4) ? s0[j] : s1[j - 4];
-        const bool ok = interior || (q_ok && key < k_end && key <= my_last);
-        sv[j] = ok ? raw * scale2 : -INFINITY;
-        mx = fmaxf(mx, sv[j]);
-      }
-      const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)));
-      // (exp2 of -inf is 0: masked keys and an empty running state drop out)
-      const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
-      uint32_t pw[4];
-#pragma unroll
-      for (int j = 0; j < 8; j += 2)
-        pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
-      // P V takes the probabilities in bf16; the normaliser (the ones rows)
-      // sums the same rounded values, so the output stays a convex
-      // combination of values
-      const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, (uint4){pw[0], pw[1], pw[2], pw[3]});
-      m_run[t] = m_new;
-      // the accumulators are rescaled only when some query's maximum rose
-      // (alpha is exactly 1 otherwise)
-      if (__ballot(alpha != 1.f) != 0ull) {
-        lacc[t] *= alpha;
-#pragma unroll
-        for (int td = 0; td < NDT; ++td) oacc[t][td] *= alpha;
-      }
-      lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, lacc[t], 0, 0, 0);
+      // values of keys kt + 8 g .. + 7, columns 16 td + rr; blocks past the key
+      // range read the range's last block (unconditional loads: a load under a
+      // lane condition makes the compiler wait for every load before it), and
+      // positions past the range are zeroed (never-written cache slots may hold
+      // NaN bits)
+      const int k8 = kt + 8 * g, nv = k_end - k8;
+      const int k8c = min(k8, (k_end - 1) & ~7);
+      uint4 vw[NDT];
 #pragma unroll
       for (int td = 0; td < NDT; ++td)
-        oacc[t][td] =
-            __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vw[td]), pb, oacc[t][td], 0, 0, 0);
+        vw[td] = __builtin_bit_cast(uint4, ld_kv<NT>((const bf16x8_t *)(vc + kvbase * DH + (size_t)(k8c >> 3) * (8 * DH) +
+                                                                         (16 * td + rr) * 8)));
+      if (!interior && nv < 8) {
+#pragma unroll
+        for (int td = 0; td < NDT; ++td) {
+          uint32_t w[4] = {vw[td].x, vw[td].y, vw[td].z, vw[td].w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (2 * i >= nv) w[i] = 0u;
+            else if (2 * i + 1 >= nv) w[i] &= 0xFFFFu;
+          }
+          vw[td] = (uint4){w[0], w[1], w[2], w[3]};
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < QT; ++t) {
+        f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+        if (DH >= 32) {
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[c], qf[t][c], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1[c], qf[t][c], s1, 0, 0, 0);
+          }
+        } else {
+          s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b0, qf16[t], s0, 0, 0, 0);
+          s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(b1, qf16[t], s1, 0, 0, 0);
+        }
+        // scores of keys kt + 8g + j, j = 0..7, for query 16 t + rr (steps
+        // wholly inside every query's visible range skip the masks; padding
+        // queries then carry finite scores of zero queries, never stored)
+        const int my_q = 16 * t + rr, my_last = base + my_q;
+        const bool q_ok = my_q < P;
+        float sv[8];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int key = kt + 8 * g + j;
+          const float raw = (j < 4) ? s0[j] : s1[j - 4];
+          const bool ok = interior || (q_ok && key < k_end && key <= my_last);
+          sv[j] = ok ? raw * scale2 : -INFINITY;
+          mx = fmaxf(mx, sv[j]);
+        }
+        const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)));
+        // (exp2 of -inf is 0: masked keys and an empty running state drop out)
+        const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
+        uint32_t pw[4];
+#pragma unroll
+        for (int j = 0; j < 8; j += 2)
+          pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
+        // P V takes the probabilities in bf16; the normaliser (the ones rows)
+        // sums the same rounded values, so the output stays a convex
+        // combination of values
+        const bf16x8_t pb = __builtin_bit_cast(bf16x8_t, (uint4){pw[0], pw[1], pw[2], pw[3]});
+        m_run[t] = m_new;
+        // the accumulators are rescaled only when some query's maximum rose
+        // (alpha is exactly 1 otherwise)
+        if (__ballot(alpha != 1.f) != 0ull) {
+          lacc[t] *= alpha;
+#pragma unroll
+          for (int td = 0; td < NDT; ++td) oacc[t][td] *= alpha;
+        }
+        lacc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb, lacc[t], 0, 0, 0);
+#pragma unroll
+        for (int td = 0; td < NDT; ++td)
+          oacc[t][td] =
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vw[td]), pb, oacc[t][td], 0, 0, 0);
+      }
     }
-  }
+  };
+  if (ROLE == 1 && n_keys >= nt_keys) steps(std::true_type{});   // (uniform)
+  else steps(std::false_type{});
   // lane (rr, g) holds O^T[16 td + 4 g + i][query 16 t + rr]
   if constexpr (NW == 8) {
     // waves 4..7 hand their state to waves 0..3 (same lane layout), which
@@ -805,8 +811,8 @@ __global__ void k_attn_combine(const float *__restrict__ part, ACT *__restrict__
 // (sequence, head) pairs alone do not fill the chip.
 template <typename ACT, int DH, int ROLE>
 static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const int32_t *start, int start_off,
-                      const int32_t *done, int B, int P, int H, int cap, float *part, int sink, hipEvent_t ev0,
-                      hipEvent_t ev1, hipStream_t s) {
+                      const int32_t *done, int B, int P, int H, int cap, float *part, int sink, int nt_keys,
+                      hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
   if (ROLE == 0 && P > ATTN_ROWS_MIN_P) {
     // a prefill chunk
     auto rows = [&](auto kern, int per_wg) {
@@ -828,19 +834,19 @@ static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const 
   const bool eight = sizeof(ACT) == 2 && splits == 2;
   if (eight) splits = 1;
   dim3 grid(B * H, 1, splits);
-  auto go = [&](auto kern, int nt) {
+  auto go = [&](auto kern, int nt, auto... more) {
     hipExtLaunchKernelGGL(kern, grid, dim3(nt), 0, s, ev0, ev1, 0, H, P, start, done, start_off, Q, Kc, Vc, O, cap,
-                          splits, part, sink);
+                          splits, part, sink, more...);
   };
   if constexpr (sizeof(ACT) == 2) {
     if (eight) {
-      if (qtiles == 1) go(k_attn_mfma<DH, ROLE, 1, 8>, 512);
-      else if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2, 8>, 512);
-      else go(k_attn_mfma<DH, ROLE, 3, 8>, 512);
+      if (qtiles == 1) go(k_attn_mfma<DH, ROLE, 1, 8>, 512, nt_keys);
+      else if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2, 8>, 512, nt_keys);
+      else go(k_attn_mfma<DH, ROLE, 3, 8>, 512, nt_keys);
     } else {
-      if (qtiles == 1) go(k_attn_mfma<DH, ROLE, 1>, 256);
-      else if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2>, 256);
-      else go(k_attn_mfma<DH, ROLE, 3>, 256);
+      if (qtiles == 1) go(k_attn_mfma<DH, ROLE, 1>, 256, nt_keys);
+      else if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2>, 256, nt_keys);
+      else go(k_attn_mfma<DH, ROLE, 3>, 256, nt_keys);
     }
   } else {
     if (qtiles == 1) go(k_attn_mfma_f32<DH, ROLE, 1>, 256);
@@ -858,37 +864,28 @@ static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const 
 template <int ROLE>
 static void attention_role(const void *q, const void *kc, const void *vc, void *o, int bf16, const int32_t *start,
                            int start_off, const int32_t *done, int B, int P, int H, int dh, int cap, float *part,
-                           int sink, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
-  if constexpr (ROLE != 2) {
-    if (!bf16) {
-      const float *Q = (const float *)q, *Kc = (const float *)kc, *Vc = (const float *)vc;
-      float *O = (float *)o;
-      switch (dh) {
-        case 16: attn_mfma<float, 16, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-        case 32: attn_mfma<float, 32, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-        default: attn_mfma<float, 64, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-      }
-      return;
-    }
-  }
-  const bf16_t *Q = (const bf16_t *)q, *Kc = (const bf16_t *)kc, *Vc = (const bf16_t *)vc;
-  bf16_t *O = (bf16_t *)o;
-  switch (dh) {
-    case 16: attn_mfma<bf16_t, 16, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-    case 32: attn_mfma<bf16_t, 32, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-    default: attn_mfma<bf16_t, 64, ROLE>(Q, Kc, Vc, O, start, start_off, done, B, P, H, cap, part, sink, ev0, ev1, s); break;
-  }
+                           int sink, int nt_keys, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
+  auto go = [&](auto act, auto width) {
+    typedef decltype(act) ACT;
+    attn_mfma<ACT, decltype(width)::value, ROLE>((const ACT *)q, (const ACT *)kc, (const ACT *)vc, (ACT *)o, start,
+                                                 start_off, done, B, P, H, cap, part, sink, nt_keys, ev0, ev1, s);
+  };
+  auto widths = [&](auto act) {
+    if (dh == 16) go(act, std::integral_constant<int, 16>{});
+    else if (dh == 32) go(act, std::integral_constant<int, 32>{});
+    else go(act, std::integral_constant<int, 64>{});
+  };
+  if (bf16) widths(bf16_t{});
+  else widths(float{});
 }
 
 void launch_attention(const void *q, const void *kc, const void *vc, void *o, int bf16, const int32_t *start,
                       int start_off, const int32_t *done, int B, int P, int H, int dh, int cap, float *part,
-                      int sink, int verify, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
-  if (verify == 2 && bf16)
-    attention_role<2>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, ev0, ev1, s);
-  else if (verify)
-    attention_role<1>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, ev0, ev1, s);
+                      int sink, int verify, int nt_keys, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s) {
+  if (verify)
+    attention_role<1>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, nt_keys, ev0, ev1, s);
   else
-    attention_role<0>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, ev0, ev1, s);
+    attention_role<0>(q, kc, vc, o, bf16, start, start_off, done, B, P, H, dh, cap, part, sink, nt_keys, ev0, ev1, s);
 }
 
 }  // namespace tppsd
