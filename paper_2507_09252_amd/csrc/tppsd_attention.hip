@@ -120,6 +120,10 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
 
   auto steps = [&](auto nt) {
     constexpr bool NT = decltype(nt)::value;
+    // the verify pass scales where the maximum is subtracted (instructions bound
+    // short contexts: 4096 sequences of some 48 events, a job 7.42 -> 7.35 ms);
+    // the other passes scale first, like k_attn_rows
+    constexpr bool FMA = ROLE == 1;
     for (int kt = k_begin + wave * KT; kt < k_end; kt += NW * KT) {
       const bool interior = kt + KT <= k_end && kt + KT <= base + 1;   // every key visible to every query
       const size_t r0 = kvbase + min(kt + krow0, cap - 1), r1 = kvbase + min(kt + krow1, cap - 1);
@@ -184,17 +188,19 @@ __global__ __launch_bounds__(64 * NW, DH <= 32 && QT == 1 && NW == 4 ? 8 : 1)
           const int key = kt + 8 * g + j;
           const float raw = (j < 4) ? s0[j] : s1[j - 4];
           const bool ok = interior || (q_ok && key < k_end && key <= my_last);
-          sv[j] = ok ? raw * scale2 : -INFINITY;
+          sv[j] = ok ? (FMA ? raw : raw * scale2) : -INFINITY;
           mx = fmaxf(mx, sv[j]);
         }
-        const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)));
+        const float m_new = fmaxf(m_run[t], xor32_max(xor16_max(mx)) * (FMA ? scale2 : 1.f));
         // (exp2 of -inf is 0: masked keys and an empty running state drop out)
         const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;
         const float alpha = __builtin_amdgcn_exp2f(m_run[t] - m_ref);
         uint32_t pw[4];
 #pragma unroll
         for (int j = 0; j < 8; j += 2)
-          pw[j >> 1] = pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
+          pw[j >> 1] = FMA ? pk2bf(__builtin_amdgcn_exp2f(fmaf(sv[j], scale2, -m_ref)),
+                                   __builtin_amdgcn_exp2f(fmaf(sv[j + 1], scale2, -m_ref)))
+                           : pk2bf(__builtin_amdgcn_exp2f(sv[j] - m_ref), __builtin_amdgcn_exp2f(sv[j + 1] - m_ref));
         // P V takes the probabilities in bf16; the normaliser (the ones rows)
         // sums the same rounded values, so the output stays a convex
         // combination of values

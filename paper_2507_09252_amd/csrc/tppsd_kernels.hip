@@ -184,7 +184,7 @@ __device__ __forceinline__ void st4(float *p, size_t i, float a, float b, float 
 __device__ __forceinline__ void st4(bf16_t *p, size_t i, float a, float b, float c, float d) {
   *(uint2 *)(p + i) = make_uint2(pk2bf(a, b), pk2bf(c, d));
 }
-template <typename ACT>
+template <typename ACT, bool TILED>
 __global__ __launch_bounds__(256) void k_layernorm(const float *__restrict__ x, ACT *__restrict__ y,
                                                    const float *__restrict__ g, const float *__restrict__ bt,
                                                    int T, int d, int P, int tile_from) {
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_layernorm(const float *__restrict__ x, 
   // tile_from on, of P per sequence; widths of 256 and more) in the order of
   // the products that normalise their own operand: over vectors of 8 columns,
   // 128 columns apart, then over the 16 vectors of 128 columns
-  const bool tiled = row % P >= tile_from;   // (one row per wave)
+  const bool tiled = TILED && row % P >= tile_from;   // (one row per wave)
   auto row_sum = [&](const float (&part)[LN_VEC_MAX]) {
     float s = 0.f;
     if (!tiled) {
@@ -4451,11 +4451,10 @@ void launch_attnhp_update(float *x, const void *o, void *u, void *a, int bf16, i
 
 void launch_layernorm(const float *x, void *y, int bf16, const float *g, const float *b, int T, int d, int P,
                       int tile_from, hipStream_t s) {
-  const int blocks = (T + 3) / 4;
-  if (bf16)
-    k_layernorm<bf16_t><<<blocks, 256, 0, s>>>(x, (bf16_t *)y, g, b, T, d, P, tile_from);
-  else
-    k_layernorm<float><<<blocks, 256, 0, s>>>(x, (float *)y, g, b, T, d, P, tile_from);
+  auto go = [&](auto kern, auto *out) { kern<<<(T + 3) / 4, 256, 0, s>>>(x, out, g, b, T, d, P, tile_from); };
+  const bool tiled = tile_from < P;
+  if (bf16) tiled ? go(k_layernorm<bf16_t, true>, (bf16_t *)y) : go(k_layernorm<bf16_t, false>, (bf16_t *)y);
+  else tiled ? go(k_layernorm<float, true>, (float *)y) : go(k_layernorm<float, false>, (float *)y);
 }
 
 bool gemm_ln_fusable(int bf16, int K) {
