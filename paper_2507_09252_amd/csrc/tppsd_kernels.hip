@@ -4477,14 +4477,15 @@ static void gemm_dispatch(const void *X, const LnA *ln, const void *W, int T, in
   const float *xf = ln ? ln->x : nullptr, *lg = ln ? ln->g : nullptr, *lb = ln ? ln->b : nullptr;
   // few rows, K a power of two of the k-steps that have an instance: 16 x 16
   // tiles, K loaded by all waves at once. What a CU takes in bounds it (48 KB a
-  // tile at K = 512), so the rule is on the rows. Measured, one AR step, this
-  // kernel against the 32 x 32 tiles below: d = 512 (8 layers) 32 rows 195 vs
-  // 321 us, 128 rows 369 vs 438, 256 rows (operands by the lanes' own loads)
-  // 696 vs 609; d = 256 (6 layers) 32 rows 115 vs 167, 128 rows 166 vs 209; fp32
-  // d = 64 (4 layers) 256 rows 120 vs 142. (32 x 32 tiles with K split the same
-  // way take in as much per CU over fewer CUs: 32 rows 306 us.)
+  // tile at K = 512), so the rule is on the rows. Measured, this kernel against
+  // the 32 x 32 tiles below, an AR step and a verify pass of that many rows: d =
+  // 512 (8 layers) 64 rows 227 vs 297 and 220 vs 285 us, 96 rows 279 vs 309 and
+  // 267 vs 291, 128 rows 318 vs 327 and 295 vs 290, 160 rows 408 vs 357 and 361 vs
+  // 306; d = 256 (6 layers) 128 rows 127 vs 169 and 116 vs 156, 256 rows 160 vs
+  // 187 and 139 vs 162; AttNHP d = 256 256 rows 103 vs 107 and 80 vs 80; d = 128
+  // 256 rows 116 vs 143 and 104 vs 129; fp32 d = 64 (4 layers) 256 rows 97 vs 119
   const int ksteps = K % MfmaStep<ELT>::KSTEP ? 0 : K / MfmaStep<ELT>::KSTEP;
-  if ((T <= 128 || (T <= 256 && K <= 256)) &&
+  if ((T <= 112 || (T <= 256 && K <= 256)) &&
       (ksteps == 4 || ksteps == 8 || ksteps == 16 || (!ln && (ksteps == 32 || ksteps == 64)))) {
     auto rows = [&](auto kern, int nw) {
       hipExtLaunchKernelGGL(kern, dim3((N + 15) / 16, (T + 15) / 16), dim3(64 * nw), 0, s, ev0, ev1, 0, x, xf, lg, lb,
@@ -4560,10 +4561,10 @@ bool layer_fused_ok(int bf16, int d, int F) { return bf16 && ((d == 128 && F == 
 
 // Where the fused layer kernel is used by default: at d = 128 from 8192 rows
 // (measured at 36864 rows against the layered kernels: verify pass 1121 ->
-// 810 us) and up to 64 rows (one or two tiles replacing four launches: the
-// 32-sequence draft, 1364 -> 1346 us per round), at d = 256 from 2048 rows
-// (at 2816 rows 501 -> 461 us)
-bool layer_fused_worth(int d, long T) { return d == 128 ? (T >= 8192 || T <= 64) : T >= 2048; }
+// 810 us), at d = 256 from 2048 rows (at 2816 rows 501 -> 461 us). Few rows are
+// the few-row products' (d = 128, 6 layers, a step or pass of 8 / 32 / 64 rows:
+// 122 / 141 / 157 us here, 92 / 94 / 96 there)
+bool layer_fused_worth(int d, long T) { return T >= (d == 128 ? 8192 : 2048); }
 
 void launch_layer_fused(const LayerArgs &a, int d, int F, bool post, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   auto go = [&](auto kern, int bm, int nw) {

@@ -1,6 +1,6 @@
 """The fused layer kernel through verify passes of B (gamma + 1) rows, against
 the oracle, with the fixed per-workload bounds of gpu_common: d = 128 (48-row
-tiles) up to 64 rows and from 8192, d = 256 in 16-row tiles up to 4096 rows and
+tiles) at a few rows and from 8192, d = 256 in 16-row tiles up to 4096 rows and
 in 32-row tiles above, ragged and whole last tiles, and head widths of 16, 32
 and 64 (the order in which keys and values are stored)."""
 import dataclasses
@@ -28,7 +28,8 @@ CASES = [Case(f"d{d}-H{H}-T{B * (g + 1)}", _wl(d, H, F), B, 20, "bias", True, g)
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c.name for c in CASES])
-def test_verify_layer_rows(case):
+def test_verify_layer_rows(case, monkeypatch):
+    monkeypatch.setenv("TPPSD_FFN_FUSED", "1")   # (a few rows run the few-row products by default)
     wt, wd = weights(case)
     ht, hk = histories(case)
     hk = hk % case.wl.target.n_types
