@@ -172,8 +172,9 @@ int tppsd_state_bytes(const tppsd_model *target, const tppsd_model *draft, int B
                       int max_events, int max_gamma, size_t *bytes);
 
 /* Creates a sampler state in the caller's workspace (256-byte aligned,
- * tppsd_state_bytes or more; a workspace short of the prefill rows alone is
- * also taken, and its prefill then runs in chunks of 16 positions). `seed` keys the Philox4x64-10 streams of every
+ * tppsd_state_bytes or more; a workspace short of prefill rows alone is also
+ * taken, and its prefill then runs in the longest chunks, of 16 positions or a
+ * multiple, that it holds). `seed` keys the Philox4x64-10 streams of every
  * draw; `flags` is a combination of TPPSD_FLAG_*. The draft model may be NULL
  * for an AR-only state. Copies a small constant table into the workspace
  * (synchronously). Errors: TPPSD_E_ARG, TPPSD_E_WORKSPACE, TPPSD_E_CONFIG,

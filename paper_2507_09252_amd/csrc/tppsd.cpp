@@ -325,8 +325,8 @@ WsLayout ws_layout(const tppsd_model *T, const tppsd_model *D, int B, int cap, i
   };
   const size_t Bz = (size_t)B;
   w.status = take(4);
-  w.n_done = take(4);
-  w.left = take(4);
+  w.n_done = take(8);   // finished sequences; most events that one still needs
+  w.left = w.n_done + 4;
   w.acc = take((size_t)B * 3 * 8);   // per-sequence counters: accepted drafts, drafted, A-R candidates
   w.n = take(Bz * 4);
   w.gen = take(Bz * 4);
@@ -1178,12 +1178,14 @@ int tppsd_state_create(const tppsd_model *T, const tppsd_model *D, int B, int ma
   if (!d_ws || !out) return fail(TPPSD_E_ARG, "null workspace or output pointer");
   if ((uintptr_t)d_ws % ALIGN) return fail(TPPSD_E_WORKSPACE, "workspace must be 256-byte aligned");
   // a smaller workspace that holds the rounds' scratch is taken too: prefill then runs in
-  // chunks of PREFILL_CHUNK positions
+  // the longest chunks of whole PREFILL_CHUNKs that it has the rows for
   size_t pre_rows = prefill_rows(B, max_events);
   if (ws_bytes < need) {
-    pre_rows = 0;
     if (ws_bytes < ws_layout(T, D, B, max_events, max_gamma, 0).total)
       return fail(TPPSD_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
+    size_t most = pre_rows / B / PREFILL_CHUNK;
+    while (most > 0 && ws_bytes < ws_layout(T, D, B, max_events, max_gamma, B * most * PREFILL_CHUNK).total) --most;
+    pre_rows = B * most * PREFILL_CHUNK;
   }
   if (flags & ~TPPSD_FLAG_BONUS) return fail(TPPSD_E_ARG, "unknown flags 0x%x", flags);
   const WsLayout w = ws_layout(T, D, B, max_events, max_gamma, pre_rows);

@@ -113,3 +113,27 @@ def test_pack_weights_roundtrip(lib):
         if bf:
             want = W.to_bf16_values(want)
         assert np.array_equal(vals, want), name
+
+
+# (workload, sequences, events, draft length, with a draft) -> bytes that have always been enough
+SIZES = [(("c1", 1, 89, 4, True), 197888), (("c2", 64, 161, 10, True), 29835520),
+         (("c4", 32, 657, 16, False), 364491776), (("c4", 5, 200, 16, True), 21170944),
+         (("a3", 100, 700, 7, True), 486657792), (("c5", 600, 90, 8, True), 258650368)]
+
+
+@pytest.mark.parametrize("shape,enough", SIZES, ids=["-".join(map(str, s)) for s, _ in SIZES])
+def test_workspace_sizes_taken(lib, shape, enough):
+    """A workspace that holds the rounds' scratch is taken, also where it is
+    short of the rows of long prefill chunks; one below is refused. (An unknown
+    flag, which is looked at after the size, stops the call there.)"""
+    name, B, cap, gamma, draft = shape
+    wl, h = W.WORKLOADS[name], [ctypes.c_void_p(), ctypes.c_void_p()]
+    for m, cfg in zip(h, (wl.target, wl.draft)):
+        assert lib.tppsd_model_create(ctypes.byref(tp.cfg_c(cfg)), ctypes.c_void_p(1 << 20), ctypes.byref(m)) == 0
+    args = (h[0], h[1] if draft else None, B, cap, gamma)
+    n, st = ctypes.c_size_t(), ctypes.c_void_p()
+    assert lib.tppsd_state_bytes(*args, ctypes.byref(n)) == 0 and n.value >= enough
+    for size, code in ((enough - 1, 3), (enough, 1), (n.value - 1, 1 if n.value > enough else 3), (n.value, 1)):
+        assert lib.tppsd_state_create(*args, 0, 8, ctypes.c_void_p(1 << 30), size, ctypes.byref(st)) == code, size
+    for m in h:
+        lib.tppsd_model_destroy(m)

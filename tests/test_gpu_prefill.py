@@ -79,33 +79,28 @@ def test_verify_after_long_prefill(case):
 @pytest.mark.parametrize("case", [small("c2", 5, n_hist=90, init="bias"), small("c3", 5, n_hist=90, init="bias")],
                          ids=["c2", "c3"])
 def test_smaller_workspace_prefills_in_short_chunks(case):
-    # one byte less than tppsd_state_bytes asks for still holds the rounds'
-    # scratch: accepted, and the same results from chunks of 16 positions
+    # a workspace that holds the rounds' scratch alone is accepted, and gives the
+    # same results from chunks of 16 positions
     wt, wd = weights(case)
     ht, hk = histories(case)
     dr = _drafts(case, ht, 6)
     st = gpu_state(case, wt, wd, case.g, 8, 3)
     want = _verify(case, st, dr, ht, hk, 8)
-    L, n, h = tp.lib(), ctypes.c_size_t(), ctypes.c_void_p()
-    args = (st.target.handle, st.draft.handle, st.B, st.max_events, st.max_gamma)
-    assert L.tppsd_state_bytes(*args, ctypes.byref(n)) == 0
-    ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
-    assert L.tppsd_state_create(*args, 3, tp.FLAG_BONUS, ws.data_ptr(), n.value - 1, ctypes.byref(h)) == 0
-    L.tppsd_state_destroy(st.handle)
-    st.handle, st.ws = h, ws
+    _shorter_state(st, 3, 0)
     got = _verify(case, st, dr, ht, hk, 8)
     tol = tol_of(case.wl)
     for f in ("logw", "mu", "s", "logtype"):
         assert np.abs(getattr(got, f) - getattr(want, f)).max() <= tol, f
 
 
-def _shortest_state(st, seed):
-    """Moves st into the smallest workspace that is taken: its prefill runs in chunks of 16 positions."""
+def _shorter_state(st, seed, share):
+    """Moves st into a workspace between the smallest that is taken (its prefill
+    runs in chunks of 16 positions; share 0) and a whole one (share 1)."""
     L, n, h = tp.lib(), ctypes.c_size_t(), ctypes.c_void_p()
     args = (st.target.handle, st.draft.handle if st.draft else None, st.B, st.max_events, st.max_gamma)
     assert L.tppsd_state_bytes(*args, ctypes.byref(n)) == 0
     ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
-    lo, hi = 0, n.value   # (refused, taken)
+    lo, hi, whole = 0, n.value, n.value   # (refused, taken)
     while hi - lo > 256:
         mid = (lo + hi) // 2
         if L.tppsd_state_create(*args, seed, tp.FLAG_BONUS, ws.data_ptr(), mid, ctypes.byref(h)) == 0:
@@ -113,7 +108,8 @@ def _shortest_state(st, seed):
             hi = mid
         else:
             lo = mid
-    assert L.tppsd_state_create(*args, seed, tp.FLAG_BONUS, ws.data_ptr(), hi, ctypes.byref(h)) == 0
+    size = hi + int(share * (whole - hi))
+    assert L.tppsd_state_create(*args, seed, tp.FLAG_BONUS, ws.data_ptr(), size, ctypes.byref(h)) == 0
     L.tppsd_state_destroy(st.handle)
     st.handle, st.ws = h, ws
 
@@ -134,12 +130,13 @@ def test_history_bits_do_not_depend_on_chunks(wl, B, n):
     hk = hk % wl.target.n_types
     print(f"{wl.name} B {B}, history {n}", flush=True)
     runs = []
-    for short in (False, True):
+    for share in (1, 0, 0.4):
         st = gpu_state(case, wt, wd, 3, 12, 3, draft=False)
-        if short:
-            _shortest_state(st, 3)
+        if share < 1:
+            _shorter_state(st, 3, share)
         st.tppsd_prefill(to_dev(ht), to_dev(hk), 12)
         st.tppsd_sample_ar(12)
         t, k, _ = st.tppsd_read_events()
         runs.append((t[:, :n + 12].cpu().numpy().view(np.uint32), k[:, :n + 12].cpu().numpy()))
-    assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
+    for t, k in runs[1:]:
+        assert np.array_equal(runs[0][0], t) and np.array_equal(runs[0][1], k)
