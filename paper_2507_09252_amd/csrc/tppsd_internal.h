@@ -259,6 +259,7 @@ struct VerifySeqArgs {
   const float *dr_t;
   const int32_t *dr_k;
   int dr_stride;
+  int fill_done;            // a finished sequence's rows too, from the new positions alone
   uint32_t *status;
   HeadArgs h;               // HEAD_VERIFY, or HEAD_AR (P = 1)
 };

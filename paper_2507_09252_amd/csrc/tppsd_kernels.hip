@@ -3674,7 +3674,7 @@ __global__ __launch_bounds__(512) void k_verify_seq(VerifySeqArgs a) {
   float *const pm = part, *const pA = part + NPM, *const pB = pA + NPA, *const hv = part;
   const int tid = threadIdx.x, b = blockIdx.x, P = a.P;
   const bool skip = a.done[b] != 0;
-  if (skip && D == 32) return;
+  if (skip && !a.fill_done) return;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rr = lane & 15, g = lane >> 4;
   const int M = a.M, K = a.K, Mt = (M + 15) / 16, Kt = (K + 15) / 16, LV = 3 * M + K + 1;
   const int pos0 = a.lenT[b];

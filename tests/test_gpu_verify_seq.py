@@ -94,3 +94,29 @@ def test_pass_follows_the_job(prec, B, n, n_gen, cap, per_seq):
         st.tppsd_prefill(to_dev(ht[:, :job[0]]), to_dev(hk[:, :job[0]] % 3), job[1])
         st.tppsd_sample_sd(4)
         assert st.tppsd_state_status()["n_done"] == B
+
+
+# n_gen = 0: every sequence is finished. The layered pass fills the caller's rows
+# all the same, from the new positions alone; so does the per-sequence pass of the
+# widths that both serve (17 positions are the layered pass's)
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+def test_finished_sequences_rows(prec):
+    from gpu_common import to_dev
+    from paper_2507_09252_amd import tppsd as tp
+    case = _case(prec, 64, 256, 2, 5, 3, 40, 16)
+    wt, wd = weights(case)
+    ht, hk = histories(case)
+    dr = _drafts(case, ht, 5)
+    rows = []
+    for g in (8, 16):
+        st = gpu_state(case, wt, wd, g, 8, 3)
+        st.tppsd_prefill(to_dev(ht), to_dev(hk % 3), 0)
+        dbuf, vbuf = tp.DraftBuffers(case.B, g, 5, 3), tp.VerifyBuffers(case.B, g, 5, 3)
+        for dst, src in ((dbuf.tau, dr.tau), (dbuf.t, dr.t), (dbuf.k, dr.k)):
+            dst.copy_(to_dev(src[:, :g]))
+        vbuf.mix.fill_(float("nan"))
+        st.tppsd_verify(g, dbuf, vbuf)
+        assert st.tppsd_state_status() == {**st.tppsd_state_status(), "bits": 0, "n_done": case.B}
+        rows.append(vbuf.mix[:, :9].cpu().numpy())
+    tol = 1e-5 if prec == "fp32" else 2e-3
+    assert np.abs(rows[0] - rows[1]).max() <= tol
