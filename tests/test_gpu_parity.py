@@ -37,9 +37,11 @@ VERIFY_CASES = [
     small("c1", 5),
     small("c2", 6),
     small("c2", 4, init="paper", mismatch=False),
-    # 517 rows: the fp32 d = 64 / F = 256 target takes the row-block kernel
-    # (packed weights) from 512 rows; 33 tiles of 16, the last ragged
     small("c2", 47, init="bias"),
+    # 17 positions (the per-sequence pass takes up to 16), 527 rows: the fp32
+    # d = 64 / F = 256 target takes the row-block kernel (packed weights) from
+    # 512 rows; 33 tiles of 16, the last ragged
+    small("c2", 31, init="bias", gamma=16),
     small("c3", 5, n_hist=40, init="bias"),
     small("c3", 3, n_hist=40, init="paper", mismatch=False),
     small("c3", 3, n_hist=40),
@@ -127,8 +129,8 @@ def test_verify_fused_layer(case, monkeypatch):
 
 
 # the row-block kernel with four waves instead of its default eight (the
-# 517-row fp32 pass runs it; the d = 32 drafts' per-step kernels too)
-BLOCK_NT_CASES = [small("c2", 47, init="bias")]
+# 527-row fp32 pass runs it; the d = 32 drafts' per-step kernels too)
+BLOCK_NT_CASES = [small("c2", 31, init="bias", gamma=16)]
 
 
 @pytest.mark.parametrize("case", BLOCK_NT_CASES, ids=_ids(BLOCK_NT_CASES))
@@ -197,7 +199,7 @@ def test_accept_teacher_forced(case, external):
 
 
 # a draft with eight heads of width 16: the one-launch draft's attention runs
-# on MFMA (the vector-ALU form serves up to four heads)
+# on MFMA (the vector-ALU form serves up to four heads: test_gpu_draft_kernels.py)
 H8 = W.Workload("h8", 7, W.ModelCfg(2, 64, 4, 256, 16, 22, "bf16"), W.ModelCfg(1, 128, 8, 256, 16, 22, "bf16"),
                 batch=8, n_gen=64, gammas=(6,), n_hist=30, history="hawkes22", description="8-head bf16 draft")
 # a three-layer row-drafting draft (d 128, four heads of 32, F 512): its middle
@@ -213,7 +215,7 @@ DRAFT_CASES = [small("c1", 8), small("c2", 8), small("c3", 16, n_hist=40, init="
 
 
 # both drafting paths: one workgroup per sequence for all gamma steps (where
-# the draft model fits it), and per-step batched kernels
+# the draft model fits it; the small ones in registers), and per-step batched kernels
 @pytest.mark.parametrize("layered", [False, True], ids=["fused", "layered"])
 @pytest.mark.parametrize("case", DRAFT_CASES, ids=_ids(DRAFT_CASES))
 def test_draft_parity(case, layered, monkeypatch):
