@@ -140,3 +140,25 @@ def test_history_bits_do_not_depend_on_chunks(wl, B, n):
         runs.append((t[:, :n + 12].cpu().numpy().view(np.uint32), k[:, :n + 12].cpu().numpy()))
     for t, k in runs[1:]:
         assert np.array_equal(runs[0][0], t) and np.array_equal(runs[0][1], k)
+
+
+# products in 128 x 128 tiles away from position 0 and in the decoder: the second
+# chunk of a history (64 + 35 positions of 255 AttNHP sequences, 256 + 43 of 64 THP
+# ones), then a verify pass of 4335 / 2112 rows; ragged last row blocks throughout
+@pytest.mark.parametrize("wl,B,n,gamma", [(W.WORKLOADS["a3"], 255, 100, 16), (WIDE, 64, 300, 32)], ids=["a3", "wide"])
+def test_tall_products_in_later_chunks(wl, B, n, gamma):
+    case = Case("tall", wl, B, n, "bias", True, gamma)
+    wt, wd = weights(case)
+    ht, hk = histories(case)
+    hk = hk % wl.target.n_types
+    print(f"{wl.name} B {B}, history {n}, gamma {gamma}", flush=True)
+    dr = _drafts(case, ht, 5)
+    got = _verify(case, gpu_state(case, wt, wd, gamma, 8, 3, draft=False), dr, ht, hk, 8)
+    rows = np.array([0, 1, B // 2, B - 2, B - 1])
+    def sub(o):
+        part = {f.name: getattr(o, f.name) for f in dataclasses.fields(o)}
+        return type(o)(**{k: None if v is None else v[rows] for k, v in part.items()})
+
+    T, dr = OModel(wl.target, wt), sub(dr)
+    want = S.verify(T, S.prefill(T, None, ht[rows], hk[rows], 8), dr, np.arange(len(rows)))
+    check_verify(sub(got), want, tol_of(wl), case.name, False, dr)
