@@ -844,20 +844,27 @@ static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const 
     hipExtLaunchKernelGGL(kern, grid, dim3(nt), 0, s, ev0, ev1, 0, H, P, start, done, start_off, Q, Kc, Vc, O, cap,
                           splits, part, sink, more...);
   };
+  // (passes other than verify come here with one query tile)
   if constexpr (sizeof(ACT) == 2) {
     if (eight) {
       if (qtiles == 1) go(k_attn_mfma<DH, ROLE, 1, 8>, 512, nt_keys);
-      else if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2, 8>, 512, nt_keys);
-      else go(k_attn_mfma<DH, ROLE, 3, 8>, 512, nt_keys);
+      else if constexpr (ROLE == 1) {
+        if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2, 8>, 512, nt_keys);
+        else go(k_attn_mfma<DH, ROLE, 3, 8>, 512, nt_keys);
+      }
     } else {
       if (qtiles == 1) go(k_attn_mfma<DH, ROLE, 1>, 256, nt_keys);
-      else if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2>, 256, nt_keys);
-      else go(k_attn_mfma<DH, ROLE, 3>, 256, nt_keys);
+      else if constexpr (ROLE == 1) {
+        if (qtiles == 2) go(k_attn_mfma<DH, ROLE, 2>, 256, nt_keys);
+        else go(k_attn_mfma<DH, ROLE, 3>, 256, nt_keys);
+      }
     }
   } else {
     if (qtiles == 1) go(k_attn_mfma_f32<DH, ROLE, 1>, 256);
-    else if (qtiles == 2) go(k_attn_mfma_f32<DH, ROLE, 2>, 256);
-    else go(k_attn_mfma_f32<DH, ROLE, 3>, 256);
+    else if constexpr (ROLE == 1) {
+      if (qtiles == 2) go(k_attn_mfma_f32<DH, ROLE, 2>, 256);
+      else go(k_attn_mfma_f32<DH, ROLE, 3>, 256);
+    }
   }
   if (splits > 1) {
     const int total = B * H * P * DH;
