@@ -5,7 +5,8 @@
 // One workgroup runs all gamma draft steps of a sequence. The model's matrices
 // are loaded once into MFMA operand registers, spread over the workgroup's
 // waves (a 64-wide, two-layer bf16 model with F = 256 is 234 fragments of 16
-// outputs x 32 inputs: 29 per wave over eight waves, 116 of the 256 registers),
+// outputs x 32 inputs: with tiles dealt out whole 32 per wave over eight waves,
+// 128 of the 256 registers),
 // so that a step's products read only the activations, from LDS. Weights are
 // the products' first operand: lane (r, g) of a result holds outputs 4 g .. + 3
 // of token r (one token, two in the first step, which re-encodes the last two
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(64 * NW) void k_draft_regs(DraftArgs a) {
   constexpr int KGF = KG < KF ? KG : KF, NF = KF / KGF;
   constexpr int WPH = NW / H;                          // waves per head
   // 64-key steps per batch: what fits beside the weights without a spill
-  constexpr int NB = sizeof(ELT) == 2 && !(D == 64 && L == 2 && !NHP) ? 4 : 2;
+  constexpr int NB = sizeof(ELT) != 2 || (D == 64 && L == 2 && !NHP) ? 2 : D == 64 && F == 256 ? 3 : 4;
   constexpr int LV = NHP ? 3 * D : 9 * D + F;          // small vectors per layer
   constexpr int NP = D == 64 ? 2 : 1;                  // registers of the residual stream per lane
   static_assert(NW % DT == 0 && NW % H == 0 && KD >= 1 && TPH >= 1 && (NHP || KF % KGF == 0), "shapes");
