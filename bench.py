@@ -458,7 +458,9 @@ def main():
             "traffic": measured_traffic("draft_rows", wl.name)}
     if tk["draft_kernel_launches"]:
         classes["draft"] = {
-            "bound": "hbm", "kernel": "k_draft_fused / k_draft_wave (one launch per round: all gamma draft steps)",
+            # (the configured one-launch drafts: registers of a workgroup up to 512 sequences, then a wave each)
+            "bound": "hbm", "kernel": ("k_draft_regs" if B <= 512 else "k_draft_wave") +
+                                      " (one launch per round: all gamma draft steps)",
             "ms": tk["draft_kernel_ms"], "launches": tk["draft_kernel_launches"],
             "per_launch": draft_kernel_bytes(wl, B, gamma, ctx), "unit": "GB/s", "peak": HBM_PEAK_GBS,
             "traffic": None}

@@ -243,7 +243,7 @@ void launch_block(const BlockArgs &a, int bf16, hipStream_t st, hipEvent_t ev0 =
 
 // Per-sequence verify pass or AR step (k_verify_seq): one workgroup runs the whole
 // target pass of one sequence's P = gamma + 1 (or 1) positions (embedding, every layer with
-// its attention, decoder, verify epilogue), the rows staying in LDS.
+// its attention, decoder, verify epilogue), the residual stream staying in registers.
 struct VerifySeqArgs {
   int P, d, F, H, L, M, K;
   FusedLayerW layer[FD_MAX_LAYERS];

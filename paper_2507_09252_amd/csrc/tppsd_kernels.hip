@@ -773,7 +773,6 @@ __global__ __launch_bounds__(64 * NW) void k_layer_fused(LayerArgs a) {
   // LayerNorm: lanes per row, rows per pass of the workgroup, values per lane, passes
   constexpr int LPR = NT / BM > 16 ? NT / BM : 16, RPP = NT / LPR, EPL = D / LPR, NP = BM / RPP;
   static_assert(TNA >= 1 && TNB >= 1 && F % FC == 0 && BM % 16 == 0 && EPL % 4 == 0, "shape");
-  
   __shared__ __attribute__((aligned(16))) float xs[BM * XLD];
   __shared__ __attribute__((aligned(16))) bf16_t as[BM * ALD];
   __shared__ __attribute__((aligned(16))) bf16_t hs[BM * HLD];
