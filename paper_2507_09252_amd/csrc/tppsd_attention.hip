@@ -493,16 +493,17 @@ __global__ __launch_bounds__(256) void k_attn_mfma_f32(int H, int P, const int32
 // event that is sampled later.
 // What bounds it: the loads of keys and values (8 KB a step at d_head 64)
 // through the L1 and their latency; they come from L2, where a (sequence, head)
-// slab of a seed history fits. A wave has a step or two at these lengths, so
+// slab of a seed history fits. Over short contexts a wave has a step or two, so
 // waves per SIMD count and not loads ahead: 32 queries and 128 registers.
 // Measured at 32 sequences x 8 heads x 511 queries of d_head 64: 38 us (with the
 // next step loaded ahead 54, in 168 registers 46; 16 queries 55, 64 queries 43;
 // a wave over all keys of its 32 queries, nothing to merge, 36), against 32
-// launches of k_attn_mfma over 16 queries each, 7.3 us on average. The grid
-// puts the block's last (longest) queries first.
+// launches of k_attn_mfma over 16 queries each, 7.3 us on average. Over longer
+// ones the keys' traffic counts, which 64 queries share. The grid puts the
+// block's last (longest) queries first.
 // ---------------------------------------------------------------------------
 template <int DH, int QT>
-__global__ __launch_bounds__(256, 4) void k_attn_rows(int H, int P, const int32_t *__restrict__ start,
+__global__ __launch_bounds__(256, QT > 2 ? 2 : 4) void k_attn_rows(int H, int P, const int32_t *__restrict__ start,
                                                    const int32_t *__restrict__ done, int start_off,
                                                    const bf16_t *__restrict__ q, const bf16_t *__restrict__ kc,
                                                    const bf16_t *__restrict__ vc, bf16_t *__restrict__ o, int cap,
@@ -826,7 +827,13 @@ static void attn_mfma(const ACT *Q, const ACT *Kc, const ACT *Vc, ACT *O, const 
                             done, start_off, Q, Kc, Vc, O, cap, sink);
     };
     if constexpr (sizeof(ACT) == 2) {
-      rows(k_attn_rows<DH, 2>, 32);
+      // (the events are the chunk's position and half of its length, histories start
+      // at 0; 256 of them: whole prefills, 32 against 64 queries per workgroup: 512
+      // events x 32 sequences of d = 512 1752 vs 1785 us, 1024 3868 vs 3790, 2560
+      // 13.5 vs 11.5 ms; 1024 x 256 of d = 256 10.0 vs 9.1; 160 x 256 of d = 128 644
+      // vs 674 us)
+      if (start_off + P / 2 > 256) rows(k_attn_rows<DH, 4>, 64);
+      else rows(k_attn_rows<DH, 2>, 32);
     } else {
       // waves of 32 queries (16 while that leaves compute units idle)
       if ((long)B * H * ((P + 127) / 128) >= 256) rows(k_attn_rows_f32<DH, 2>, 128);

@@ -122,7 +122,9 @@ NHP128 = dataclasses.replace(W.WORKLOADS["a3"], target=W.ModelCfg(2, 128, 4, 0, 
 # Widths of 512: chunks of 16 positions below and from 512 rows (LayerNorm in the
 # product or before it), a ragged end of 1 to 15 positions on either side of that
 @pytest.mark.parametrize("wl,B,n", [(WIDE, 5, 18), (WIDE, 5, 143), (WIDE, 31, 66), (WIDE, 33, 113), (WIDE, 33, 128),
-                                    (WIDE, 40, 126), (NHP128, 7, 100)])
+                                    (WIDE, 40, 126), (NHP128, 7, 100),
+                                    # from 256 events half-way through a chunk 64 queries per workgroup
+                                    (WIDE, 3, 540), (NHP128, 3, 600)])
 def test_history_bits_do_not_depend_on_chunks(wl, B, n):
     case = Case("chunks", wl, B, n, "bias", True)
     wt, wd = weights(case)
