@@ -4451,9 +4451,11 @@ void launch_attnhp_update(float *x, const void *o, void *u, void *a, int bf16, i
 void launch_layernorm(const float *x, void *y, int bf16, const float *g, const float *b, int T, int d, int P,
                       int tile_from, hipStream_t s) {
   auto go = [&](auto kern, auto *out) { kern<<<(T + 3) / 4, 256, 0, s>>>(x, out, g, b, T, d, P, tile_from); };
-  const bool tiled = tile_from < P;
-  if (bf16) tiled ? go(k_layernorm<bf16_t, true>, (bf16_t *)y) : go(k_layernorm<bf16_t, false>, (bf16_t *)y);
-  else tiled ? go(k_layernorm<float, true>, (float *)y) : go(k_layernorm<float, false>, (float *)y);
+  // (the order matters in 16 bits only, and only bf16 has products that normalise their operand at the widths
+  // of a LayerNorm of its own)
+  if (!bf16) go(k_layernorm<float, false>, (float *)y);
+  else if (tile_from < P) go(k_layernorm<bf16_t, true>, (bf16_t *)y);
+  else go(k_layernorm<bf16_t, false>, (bf16_t *)y);
 }
 
 bool gemm_ln_fusable(int bf16, int K) {
