@@ -354,14 +354,18 @@ WsLayout ws_layout(const tppsd_model *T, const tppsd_model *D, int B, int cap, i
   const size_t fmax = std::max(T->cfg.d_ffn, D ? D->cfg.d_ffn : 0);
   const size_t mmax = std::max(T->cfg.n_mix, D ? D->cfg.n_mix : 0);
   const size_t kmax = std::max(T->cfg.n_types, D ? D->cfg.n_types : 0);
-  const size_t Tp = std::max(Tm, pre_rows);   // (the decoder's e and logits: no prefill row reaches it)
-  w.x = take(Tp * dmax * 4);
-  w.a = take(Tp * dmax * 4);
-  w.q = take(Tp * dmax * 4);
-  w.o = take(Tp * dmax * 4);
-  w.hid = take(Tp * fmax * 4);
+  // a round's rows at 4 bytes an element, a prefill chunk's at what they hold (the decoder's e
+  // and logits: no prefill row reaches them)
+  const size_t act = std::max(T->act_bytes(), D ? D->act_bytes() : 0);
+  const bool nhp = T->attnhp() || (D && D->attnhp());
+  auto rows = [&](size_t width, size_t elt) { return std::max(Tm * width * 4, pre_rows * width * elt); };
+  w.x = take(rows(dmax, 4));
+  w.a = take(rows(dmax, act));
+  w.q = take(rows(dmax, act));
+  w.o = take(rows(dmax, act));
+  w.hid = take(rows(fmax, act));
   w.e = take(Tm * 4 * dmax * 4);
-  w.u = take(Tp * 2 * dmax * 4);   // AttNHP layer input [z; h]
+  w.u = take(rows(2 * dmax, nhp ? act : 0));   // AttNHP layer input [z; h]
   w.logits = take(Tm * head_ldl((int)mmax, (int)kmax) * 4);
   w.hwT = take((size_t)(3 * T->cfg.n_mix + T->cfg.n_types) * 4 * T->d() * T->act_bytes());
   w.hbT = take((size_t)(3 * T->cfg.n_mix + T->cfg.n_types) * 4);
